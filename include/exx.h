@@ -70,7 +70,10 @@ typedef struct {
   double cg_tol;              /* stop when ||r||_2 <= cg_tol ||b||_2 (FP64 residual)  */
   int cg_max_iter;            /* per solve; hitting it is reported as EXX_ENOCONV
                                  (a pair that converges on its last permitted
-                                 iteration counts as converged)                     */
+                                 iteration counts as converged).  A cap below 8
+                                 (2 R + 1) iterations, R the sphere's radius in
+                                 points, counts plain CG iterations: such a plan
+                                 solves without the preconditioner               */
   /* variable sphere radii: with per-orbital radii passed to exx_eval, the pair
      radius is the rung R_PE_min + k R_PE_step (k < R_PE_nclass) nearest to
      (R_i + R_j)/2; R_PE_nclass <= 0 keeps the single plan radius R_PE          */
@@ -93,8 +96,10 @@ typedef struct {
                                  tuned/default); 768 applies to quad-layout
                                  classes of at most 768 runs only, other classes
                                  keep their default                              */
-  int solve_depth;            /* planes of loads in flight ahead of use, 1 or 2
-                                 (0: tuned/default); cells with arms leaving the
+  int solve_depth;            /* 0: preconditioned CG (plain where its buffers do
+                                 not fit, at the tuned/default depth); 1 or 2:
+                                 plain CG with that many planes of loads in
+                                 flight ahead of use; cells with arms leaving the
                                  sweep plane have depth 1 only (reported as 1)    */
   int autotune;               /* 1: the first exx_eval times the CG variants on a
                                  sample of each sphere class's pairs and keeps
@@ -259,7 +264,8 @@ typedef struct {
   double eval_ms;              /* device time of the whole evaluation              */
   double cg_alg_bytes;         /* algorithmic CG bytes: sum over pairs of (8 iters
                                   - 2 fused quad sweeps - 2 passes that left x
-                                  alone) N_PE b                                     */
+                                  alone) N_PE b; preconditioned CG: 7.5 iters, or
+                                  5.5 without a stored A p                          */
   double moment_flops;         /* algorithmic moment flops: 2 N_lm N_PE per pair   */
   /* running totals since the plan was made (every completed exx_eval):       */
   long long n_evals;
@@ -275,7 +281,8 @@ typedef struct {
   int solve_threads;           /* CG variant in use: workgroup size (quad layout:
                                   768 and 512 with fused sweeps, 512 with two
                                   runs per thread) ...                             */
-  int solve_depth;             /* ... and load depth (chosen by the autotuner)     */
+  int solve_depth;             /* ... and load depth (chosen by the autotuner;
+                                  preconditioned CG: 1)                            */
   double tune_ms;              /* time spent by the autotuner (first eval only)    */
   double moment_ms;            /* device time of the moment kernels (last eval)    */
   double moment_mfma_flops;    /* flops the matrix cores executed for the moments

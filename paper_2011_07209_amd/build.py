@@ -11,7 +11,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libexx.so")
 SOURCES = ["plan_geometry.cpp", "nk_stencil.cpp", "kernels.hip", "moments.hip", "finalize.hip", "solve.hip", "solve_n1.hip",
-           "solve_n2.hip", "solve_n3.hip", "api.hip"]
+           "solve_n2.hip", "solve_n3.hip", "pcg_n1_f64.hip", "pcg_n2_f64.hip", "pcg_n3_f64.hip", "pcg_n1_mixed.hip",
+           "pcg_n2_mixed.hip", "pcg_n3_mixed.hip", "api.hip"]
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [
@@ -46,7 +47,7 @@ def build(verbose: bool = False) -> str:
             raise RuntimeError(f"hipcc failed for {src}:\n{r.stdout}\n{r.stderr}")
         return obj
 
-    with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
+    with ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1)) as ex:
         objs = list(ex.map(compile_one, SOURCES))
     tmp = LIB + ".tmp%d" % os.getpid()
     cmd = [hipcc, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]

@@ -284,16 +284,45 @@ static bool tilted_arms(const Geo& g) {
   return false;
 }
 
-exx_status apply_solve_variants(exx_plan_t P) {
+// Workgroups per CU of class k's solve with a variant (0: it cannot run the class).
+int class_groups_per_cu(exx_plan_t P, int k, int threads, int depth) {
   const bool mixed = P->opt.precision == EXX_PREC_MIXED;
+  const ClassHost& C = P->classes[k];
+  if (P->class_pcg[k]) return depth == 1 ? pcg_groups_per_cu(P->geo, C, mixed, threads) : 0;
+  return solve_groups_per_cu(P->geo, C.n_cols, C.Zmax, mixed, C.quads, threads, depth);
+}
+
+// Bytes of a workgroup's slot: the largest that a class's solver needs.
+long long plan_slot_bytes(exx_plan_t P) {
+  const bool mixed = P->opt.precision == EXX_PREC_MIXED;
+  long long b = solve_slot_bytes(mixed, slot_stride(P));
+  if (!P->pcg_off)
+    for (char on : P->class_pcg)
+      if (on) return std::max(b, pcg_slot_bytes(mixed, slot_stride(P), P->max_c1, P->max_b2));
+  return b;
+}
+
+// The class's layout and solver in the arguments of its launch.
+void class_solve_args(exx_plan_t P, int k, SolveArgs* a) {
+  const ClassHost& C = P->classes[k];
+  a->quads = C.quads;
+  a->pcg_cols = 0;
+  if (P->class_pcg[k] && !P->pcg_off) {
+    a->pcg_cols = (int)C.fin_cols.size();
+    a->mg = C.mg;
+    a->c1stride = P->max_c1;
+    a->b2stride = P->max_b2;
+  }
+}
+
+exx_status apply_solve_variants(exx_plan_t P) {
   const size_t ncls = P->classes.size();
   P->class_groups.assign(ncls, 0);
   int slots = 0;
   for (size_t k = 0; k < ncls; ++k) {
     const ClassHost& C = P->classes[k];
     if (!C.quads && tilted_arms(P->geo)) P->class_depth[k] = 1;
-    const int per_cu =
-        solve_groups_per_cu(P->geo, C.n_cols, C.Zmax, mixed, C.quads, P->class_threads[k], P->class_depth[k]);
+    const int per_cu = class_groups_per_cu(P, (int)k, P->class_threads[k], P->class_depth[k]);
     if (per_cu < 1) return fail(P, EXX_EDEVICE, "solve kernel cannot be resident (occupancy 0)");
     P->class_groups[k] = P->opt.solve_groups > 0 ? P->opt.solve_groups : P->n_cus * per_cu;
     slots = std::max(slots, P->class_groups[k]);
@@ -322,7 +351,7 @@ exx_status select_solve(exx_plan_t P, int threads, int depth, int cls) {
 exx_status ensure_slots(exx_plan_t P) {
   if (P->slot_ws) return EXX_OK;
   char* sw = nullptr;
-  const long long sb = solve_slot_bytes(P->opt.precision == EXX_PREC_MIXED, slot_stride(P));
+  const long long sb = plan_slot_bytes(P);
   if (dev_alloc(P, &sw, (size_t)P->n_slots * sb, "CG vectors")) return EXX_ENOMEM;
   P->slot_ws = sw;
   return EXX_OK;
@@ -341,7 +370,7 @@ exx_status launch_solves(exx_plan_t P, SolveArgs a, hipStream_t s) {
     a.threads = P->class_threads[k];
     a.depth = P->class_depth[k];
     if (P->class_delta[k] > 0.0) a.delta = P->class_delta[k];   // chosen by the autotuner
-    a.quads = C.quads;
+    class_solve_args(P, k, &a);
     EXX_HIP(P, launch_set_int(P->queue, 0, s));
     long long groups = std::min<long long>(P->class_groups[k], a.npair);
     if (P->slot_limit > 0) groups = std::min<long long>(groups, P->slot_limit);   // CG slots of the scratch layout
@@ -383,9 +412,7 @@ exx_status autotune_solve(exx_plan_t P, const SolveArgs& base, long long nb, hip
     // depth) and threshold delta, or a negative value when it cannot run
     auto trial = [&](int threads, int depth, double delta, float* per_pair) -> exx_status {
       *per_pair = -1.0f;
-      if (solve_groups_per_cu(P->geo, P->classes[k].n_cols, P->classes[k].Zmax, base.mixed, P->classes[k].quads,
-                              threads, depth) < 1)
-        return EXX_OK;
+      if (class_groups_per_cu(P, k, threads, depth) < 1) return EXX_OK;
       exx_status st = select_solve(P, threads, depth, k);
       if (st != EXX_OK) return st;
       st = ensure_slots(P);
@@ -400,7 +427,7 @@ exx_status autotune_solve(exx_plan_t P, const SolveArgs& base, long long nb, hip
       a.threads = threads;
       a.depth = depth;
       a.delta = delta;
-      a.quads = P->classes[k].quads;
+      class_solve_args(P, k, &a);
       Batch B;
       B.cls = P->class_dev;
       B.pairs = P->pairs;
@@ -426,7 +453,8 @@ exx_status autotune_solve(exx_plan_t P, const SolveArgs& base, long long nb, hip
     int bt = P->class_threads[k], bd = P->class_depth[k];
     int order[7][2] = {{bt, bd}};
     int nc = 1;
-    const bool one_depth = !P->classes[k].quads && tilted_arms(P->geo);   // no deeper variant to try
+    // no deeper variant to try
+    const bool one_depth = P->class_pcg[k] || (!P->classes[k].quads && tilted_arms(P->geo));
     for (const auto& c : cand)
       if ((c[0] != bt || c[1] != bd) && !(one_depth && c[1] != 1)) {
         order[nc][0] = c[0];
@@ -764,6 +792,10 @@ exx_status assemble_cell(exx_plan_t P, const double h[9]) {
              align(C.fin_cols.size() * sizeof(int4)) + align(C.rhs_ptr.size() * sizeof(int)) +
              align(C.rhs_ent.size() * sizeof(int2)) + align(C.me_scan.size() * sizeof(int)) +
              align(C.scan_off.size() * sizeof(short4)) + align(C.rhs_edge.size() * sizeof(unsigned)) + mom_bytes(C) +
+             align(C.c1cols.size() * sizeof(int4)) + align(C.c2cols.size() * sizeof(int4)) +
+             align(C.c1start.size() * sizeof(int)) + align(C.mg_pts[0].size() * sizeof(short4)) +
+             align(C.mg_pts[1].size() * sizeof(short4)) + align(C.mg_pts[2].size() * sizeof(short4)) +
+             align(C.mg_pts[3].size() * sizeof(short4)) +
              align((size_t)((C.n_halo + 15) / 16) * ((g.n_lm + 3) / 4) * 64 * sizeof(double));
   }
   void* block = nullptr;
@@ -820,6 +852,15 @@ exx_status assemble_cell(exx_plan_t P, const double h[9]) {
     D.me_scan = (const int*)put(C.me_scan.data(), C.me_scan.size() * sizeof(int));
     D.scan_off = (const short4*)put(C.scan_off.data(), C.scan_off.size() * sizeof(short4));
     D.n_scan = (long long)C.me_scan.size();
+    D.mg = C.mg;
+    D.mg.c1cols = (const int4*)put(C.c1cols.data(), C.c1cols.size() * sizeof(int4));
+    D.mg.c2cols = (const int4*)put(C.c2cols.data(), C.c2cols.size() * sizeof(int4));
+    D.mg.c1start = (const int*)put(C.c1start.data(), C.c1start.size() * sizeof(int));
+    D.mg.p1 = (const short4*)put(C.mg_pts[0].data(), C.mg_pts[0].size() * sizeof(short4));
+    D.mg.p2 = (const short4*)put(C.mg_pts[1].data(), C.mg_pts[1].size() * sizeof(short4));
+    D.mg.p3 = (const short4*)put(C.mg_pts[2].data(), C.mg_pts[2].size() * sizeof(short4));
+    D.mg.p4 = (const short4*)put(C.mg_pts[3].data(), C.mg_pts[3].size() * sizeof(short4));
+    if (!D.mg.c1cols || !D.mg.c1start || !D.mg.p1) D.mg.n_c1 = 0;
     D.mom_rows = mom_rows;
     std::vector<double> btab;
     build_boundary_table(C, g.A, g.ylm_norm, P->l_max, &btab);
@@ -868,6 +909,13 @@ exx_status assemble_cell(exx_plan_t P, const double h[9]) {
   P->max_fin = 0;
   for (const ClassHost& C : P->classes) P->max_fin = std::max<long long>(P->max_fin, (long long)C.fin_cols.size());
   P->max_zmax = max_zmax;
+  P->max_c1 = P->max_b2 = 0;
+  for (const ClassHost& C : P->classes) {
+    P->max_c1 = std::max<long long>(P->max_c1, (long long)C.mg_pts[0].size());
+    P->max_b2 = std::max<long long>(P->max_b2, (long long)C.mg.D2[0] * C.mg.D2[1] * C.mg.D2[2]);
+  }
+  P->max_c1 = (P->max_c1 + 7) / 8 * 8;
+  P->max_b2 = (P->max_b2 + 7) / 8 * 8;
   std::memcpy(P->h, h, sizeof(P->h));
   std::memcpy(P->h0, h, sizeof(P->h0));
   P->cell_strain = 0.0;
@@ -892,22 +940,39 @@ void default_solve_variants(exx_plan_t P) {
   P->class_threads.assign(P->classes.size(), 1024);
   P->class_depth.assign(P->classes.size(), dp);
   P->class_delta.assign(P->classes.size(), 0.0);
+  P->class_pcg.assign(P->classes.size(), 0);
   for (size_t k = 0; k < P->classes.size(); ++k) {
     const int nc = P->classes[k].n_cols;
+    int t = (opt.solve_threads == 512 || opt.solve_threads == 1024) ? opt.solve_threads : 0;
+    if (P->classes[k].quads && opt.solve_threads == 768 && nc <= 4 * 768) t = 768;
+    // The preconditioned CG wherever its buffers fit, unless solve_depth names a
+    // load depth of the plain CG (the sweep has one) or cg_max_iter lies below
+    // twice what the plain CG needs (about four iterations per point of the
+    // sphere's diameter): such a cap asks for that many plain CG steps.
+    // Untuned, quad classes of mixed plans take the sweep without a stored q (768
+    // threads, or 512), other classes 1024 threads up to 3 columns each.
+    P->class_pcg[k] = opt.solve_depth == 0 && opt.cg_max_iter >= 8 * (2 * P->classes[k].Zmax + 1) &&
+                      pcg_supported(P->geo, P->classes[k], opt.precision == EXX_PREC_MIXED);
+    if (P->class_pcg[k]) {
+      const int cols = (int)P->classes[k].fin_cols.size();
+      P->class_threads[k] = t ? t
+                            : P->classes[k].quads && opt.precision == EXX_PREC_MIXED ? (nc <= 4 * 768 ? 768 : 512)
+                            : cols <= 3 * 1024 ? 1024
+                                               : 512;
+      P->class_depth[k] = 1;
+      continue;
+    }
     if (P->classes[k].quads) {
       // mixed plans fuse each pass B with the next pass A in workgroups of
       // 768 (one run per thread) or 512 threads (two runs per thread)
-      int t = opt.precision == EXX_PREC_MIXED ? (nc <= 4 * 768 ? 768 : 512) : 1024;
-      if (opt.solve_threads == 512 || opt.solve_threads == 1024 || (opt.solve_threads == 768 && nc <= 4 * 768))
-        t = opt.solve_threads;
+      if (!t) t = opt.precision == EXX_PREC_MIXED ? (nc <= 4 * 768 ? 768 : 512) : 1024;
       P->class_threads[k] = t;
       // two runs per thread: loads one plane ahead (the registers of a
       // second plane of loads cost more than they hide)
       if (t == 512 && opt.solve_depth == 0) P->class_depth[k] = 1;
       continue;
     }
-    P->class_threads[k] = (opt.solve_threads == 512 || opt.solve_threads == 1024) ? opt.solve_threads
-                          : (nc <= cpt * 1024 ? 1024 : 512);
+    P->class_threads[k] = t ? t : (nc <= cpt * 1024 ? 1024 : 512);
   }
 }
 
@@ -1022,7 +1087,7 @@ size_t scratch_carve(exx_plan_t P, char* base, int n_orb, long long k, int g, Ev
   w->Qp_ws = (double*)take(sizeof(double) * (size_t)(w->qp_rows * kMaxLM));
   w->n_slots = g;
   w->slot_ws =
-      take((size_t)g * (size_t)solve_slot_bytes(P->opt.precision == EXX_PREC_MIXED, slot_stride(P)));
+      take((size_t)g * (size_t)plan_slot_bytes(P));
   return off;
 }
 
@@ -1482,11 +1547,14 @@ exx_status exx_eval_noalloc(exx_plan_t P, int n_orb, const void* orbitals, exx_d
   auto bytes_for = [&](long long k) {
     return scratch_carve(P, nullptr, n_orb, k, (int)std::min<long long>(k, max_groups), &w);
   };
-  if (bytes_for(1) > kScratchBytes)
+  // (the preconditioned CG's slots are larger: where one does not fit, this call runs the plain CG)
+  P->pcg_off = bytes_for(1) > kScratchBytes;
+  if (bytes_for(1) > kScratchBytes) {
     return fail(P, EXX_EINVAL, "exx_eval_noalloc: one pair's workspace with " + std::to_string(n_orb) +
                                    " orbitals and max_pairs " + std::to_string(span) + " needs " +
                                    std::to_string(bytes_for(1)) + " bytes, beyond the scratch array's " +
                                    std::to_string(kScratchBytes));
+  }
   while (lo < hi) {   // largest k in [1, hi] that fits
     const long long mid = (lo + hi + 1) / 2;
     if (bytes_for(mid) <= kScratchBytes) lo = mid; else hi = mid - 1;
@@ -1506,6 +1574,7 @@ exx_status exx_eval_noalloc(exx_plan_t P, int n_orb, const void* orbitals, exx_d
   P->no_alloc = false;
   P->batch_limit = 0;
   P->slot_limit = 0;
+  P->pcg_off = false;
   return st;
 }
 

@@ -22,6 +22,7 @@ constexpr double kSlack = 1e-12;               // relative slack of sphere membe
 // y-neighbour reads use immediate offsets.  It bounds the sphere:
 // 2 (R_PE / spacing + n) + 1 <= 88.
 constexpr int kLdsWX = 88;
+constexpr int kPcgRing = 4;   // directions a preconditioned solve keeps before x takes their steps
 
 // Geometry and stencil constants, passed by value to every kernel.
 struct Geo {
@@ -59,6 +60,27 @@ struct NkArm {
   int u[3];
   double beta;
   double step;
+};
+
+// The nested grids of a class's multilevel preconditioner (pcg_impl.h), in the
+// CG frame: level l holds the sphere's points whose offsets are multiples of
+// 2^l, at coordinates offset / 2^l.
+struct MgDev {
+  int n_c1, n_c2;          // columns of levels 1 and 2 (n_c1 0: no tables)
+  const int4* c1cols;      // (X, Y, lo, hi), sorted by max(|lo|, |hi|) descending
+  const int* c1start;      // [2 Z1 + 2] first slot of level-1 plane Z (index Z + Z1)
+  int Z1;                  // largest |Z| of level 1
+  const int4* c2cols;
+  const short4* p1;        // level-1 slots (w = 1: padding)
+  const short4* p2;        // the points of levels 2, 3 and 4
+  const short4* p3;
+  const short4* p4;
+  int n_p1, n_p2, n_p3, n_p4;
+  // staged planes: the sphere's with a border of one point, and level 1's
+  int rcx, rcy, rw, rh;
+  int ex, ey, ew, eh;
+  // boxes of levels 2, 3, 4: half-widths and dims 2 E + 3
+  int E2[3], D2[3], E3[3], D3[3], E4[3], D4[3];
 };
 
 // A sphere class (one PE radius).  All arrays live in one device block.
@@ -121,6 +143,7 @@ struct ClassDev {
   const double* mom_f64;
   const unsigned short* mom_hi;
   const unsigned short* mom_lo;
+  MgDev mg;
 };
 
 struct PairDev {
@@ -151,6 +174,11 @@ struct ClassHost {
   std::vector<int> me_scan;                  // the live ME entries in grid raster order (z, y, x)
   std::vector<short4> scan_off;              // their offsets, in that order
   long long n_pe = 0, n_halo = 0, n_me = 0, n_real = 0;
+  // the preconditioner's nested grids (dims in mg, whose pointers are null here)
+  MgDev mg = {};
+  std::vector<int4> c1cols, c2cols;
+  std::vector<int> c1start;
+  std::vector<short4> mg_pts[4];   // levels 1 (slots, with padding) to 4
 };
 
 // Builds the tables of one class of an orthorhombic cell; returns an empty
@@ -167,6 +195,8 @@ std::string build_class(const double L[3], const int N[3], double R_PE, double R
 void build_sweep_tables(int n, ClassHost* out);
 // The D scatter's order of a class (both builders call it): me_scan.
 void build_scan_order(ClassHost* out);
+// The nested grids of a class's preconditioner (both builders call it).
+void build_coarse_grids(ClassHost* out);
 // The same for a general cell h with the NK arms of its Laplacian; the CG
 // sweeps along grid axis `sweep`.
 // all_dirs: Dirichlet points along every nearest-neighbour direction (for
@@ -241,6 +271,7 @@ struct exx_plan_s {
   int self_class = -1;   // class of the self pairs when they have their own radii
   long long max_pe = 0, max_halo = 0, max_me = 0, max_cols = 0;
   long long max_fin = 0;   // most real columns of a class (orthorhombic; the E/sigma sweep)
+  long long max_c1 = 0, max_b2 = 0;   // most level-1 slots and level-2 box cells of a class
   long long rstride = 0;   // row stride of the per-pair workspaces: max_pe rounded up to 32
   int max_zmax = 0;
 
@@ -290,6 +321,8 @@ struct exx_plan_s {
   std::vector<int> class_threads;  // CG variant of each class: workgroup size ...
   std::vector<int> class_depth;    // ... and load depth
   std::vector<double> class_delta; // ... and (mixed) reliable-update threshold; 0: the plan's
+  std::vector<char> class_pcg;     // 1: the class runs the preconditioned CG (pcg_impl.h)
+  bool pcg_off = false;            // this call's scratch array has no room for its vectors
   int n_cus = 1;
   int solve_threads = 1024, solve_depth = 1;   // CG variant in use
   bool tuned = false;

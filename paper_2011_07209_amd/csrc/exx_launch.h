@@ -92,6 +92,11 @@ struct SolveArgs {
   int threads = 1024;          // workgroup size of the solve (512 or 1024)
   int depth = 1;               // planes of loads in flight ahead of their use (1 or 2)
   bool quads = false;          // the class's vectors are in the quad layout
+  // preconditioned CG: the class's real columns (0: plain CG), the dims of its
+  // nested grids, and the strides of a slot's level-1 vector and level-2 box
+  int pcg_cols = 0;
+  MgDev mg = {};
+  long long c1stride = 0, b2stride = 0;
 };
 
 hipError_t launch_rhs(const Geo& g, const Batch& B, long long max_pe, const double* rho_ws, double* b_ws,
@@ -101,6 +106,12 @@ size_t solve_lds_bytes(const Geo& g, int max_zmax);
 int solve_groups_per_cu(const Geo& g, int max_cols, int max_zmax, bool mixed, bool quads, int threads, int depth);
 bool solve_supported(int max_cols, int threads);
 long long solve_slot_bytes(bool mixed, long long sstride);
+// The preconditioned CG (pcg_impl.h): whether it can run a class (its staged
+// planes fit the LDS and its nested grids' columns a workgroup), its workgroups
+// per CU (0: this variant cannot run it) and its slot size.
+bool pcg_supported(const Geo& g, const ClassHost& C, bool mixed);
+int pcg_groups_per_cu(const Geo& g, const ClassHost& C, bool mixed, int threads);
+long long pcg_slot_bytes(bool mixed, long long sstride, long long c1stride, long long b2stride);
 hipError_t launch_finalize(const Geo& g, const Batch& B, const double* rho_ws, const double* v_ws, long long rstride,
                            const double* halo_ws, long long hstride, double* outE, double* outS, hipStream_t s);
 // E_xx and sigma_xx of the batch's pairs as one plane sweep per pair

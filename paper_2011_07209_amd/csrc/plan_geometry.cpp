@@ -257,6 +257,7 @@ std::string build_class(const double L[3], const int N[3], double R_PE, double R
   for (int a = 0; a < 3; ++a) C.Rc[a] = C.Rg[a];
   build_sweep_tables(n, &C);
   build_scan_order(&C);
+  build_coarse_grids(&C);
   return std::string();
 }
 
@@ -274,6 +275,90 @@ void build_scan_order(ClassHost* out) {
   });
   C.scan_off.resize(C.me_scan.size());
   for (size_t k = 0; k < C.me_scan.size(); ++k) C.scan_off[k] = C.me_off[(size_t)C.me_scan[k]];
+}
+
+void build_coarse_grids(ClassHost* out) {
+  ClassHost& C = *out;
+  // level l's points, in the CG frame: a sphere point whose offsets are all
+  // multiples of 2^l
+  std::vector<std::array<int, 3>> lev[4];
+  for (long long k = 0; k < C.n_pe; ++k) {
+    const short4 o = C.me_off[(size_t)k];
+    if (o.w) continue;
+    const int t[3] = {o.x, o.y, o.z};
+    const int v[3] = {t[C.perm[0]], t[C.perm[1]], t[C.perm[2]]};
+    for (int l = 0; l < 4; ++l) {
+      const int m = (2 << l) - 1;
+      if ((v[0] & m) || (v[1] & m) || (v[2] & m)) break;
+      lev[l].push_back({v[0] >> (l + 1), v[1] >> (l + 1), v[2] >> (l + 1)});
+    }
+  }
+  // columns of levels 1 and 2: along a line through a convex set the points
+  // are an interval
+  auto columns = [](const std::vector<std::array<int, 3>>& pts) {
+    std::vector<std::array<int, 3>> p = pts;
+    std::sort(p.begin(), p.end(), [](const auto& a, const auto& b) {
+      if (a[1] != b[1]) return a[1] < b[1];
+      if (a[0] != b[0]) return a[0] < b[0];
+      return a[2] < b[2];
+    });
+    std::vector<int4> cols;
+    for (const auto& q : p) {
+      if (!cols.empty() && cols.back().x == q[0] && cols.back().y == q[1])
+        cols.back().w = q[2];
+      else
+        cols.push_back(make_int4(q[0], q[1], q[2], q[2]));
+    }
+    std::stable_sort(cols.begin(), cols.end(), [](const int4& a, const int4& b) {
+      return std::max(std::abs(a.z), std::abs(a.w)) > std::max(std::abs(b.z), std::abs(b.w));
+    });
+    return cols;
+  };
+  MgDev& M = C.mg;
+  M = MgDev();
+  C.c1cols = columns(lev[0]);
+  C.c2cols = columns(lev[1]);
+  M.n_c1 = (int)C.c1cols.size();
+  M.n_c2 = (int)C.c2cols.size();
+  M.Z1 = 0;
+  for (const int4& c : C.c1cols) M.Z1 = std::max(M.Z1, std::max(std::abs(c.z), std::abs(c.w)));
+  // level-1 slots plane by plane, each plane the prefix of the columns that reach it
+  C.c1start.assign(2 * M.Z1 + 2, 0);
+  for (int l = 0; l < 4; ++l) C.mg_pts[l].clear();
+  for (int z = -M.Z1; z <= M.Z1; ++z) {
+    C.c1start[z + M.Z1] = (int)C.mg_pts[0].size();
+    for (const int4& c : C.c1cols) {
+      if (std::max(std::abs(c.z), std::abs(c.w)) < std::abs(z)) break;
+      const bool in = z >= c.z && z <= c.w;
+      C.mg_pts[0].push_back(make_short4((short)c.x, (short)c.y, (short)z, in ? 0 : 1));
+    }
+  }
+  C.c1start[2 * M.Z1 + 1] = (int)C.mg_pts[0].size();
+  for (int l = 1; l < 4; ++l)
+    for (const auto& q : lev[l]) C.mg_pts[l].push_back(make_short4((short)q[0], (short)q[1], (short)q[2], 0));
+  M.n_p1 = (int)C.mg_pts[0].size();
+  M.n_p2 = (int)C.mg_pts[1].size();
+  M.n_p3 = (int)C.mg_pts[2].size();
+  M.n_p4 = (int)C.mg_pts[3].size();
+  M.rcx = C.Rc[0] + 1;
+  M.rcy = C.Rc[1] + 1;
+  M.rw = 2 * M.rcx + 1;
+  M.rh = 2 * M.rcy + 1;
+  M.ex = (C.Rc[0] + 1) >> 1;
+  M.ey = (C.Rc[1] + 1) >> 1;
+  M.ew = 2 * M.ex + 3;
+  M.eh = 2 * M.ey + 3;
+  // half-widths: every interpolation from level l reaches at most one cell past
+  // the halved extent of level l - 1
+  const int e1[3] = {M.ex, M.ey, (C.Zmax + 1) >> 1};
+  for (int a = 0; a < 3; ++a) {
+    M.E2[a] = (e1[a] + 1) >> 1;
+    M.E3[a] = (M.E2[a] + 1) >> 1;
+    M.E4[a] = (M.E3[a] + 1) >> 1;
+    M.D2[a] = 2 * M.E2[a] + 3;
+    M.D3[a] = 2 * M.E3[a] + 3;
+    M.D4[a] = 2 * M.E4[a] + 3;
+  }
 }
 
 void build_sweep_tables(int n, ClassHost* out) {
@@ -617,6 +702,7 @@ std::string build_class_general(const double h[9], const int N[3], int sweep, do
       }
   C.n_me = (long long)C.me_off.size();
   build_scan_order(&C);
+  build_coarse_grids(&C);
   return std::string();
 }
 

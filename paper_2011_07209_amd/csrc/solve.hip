@@ -1,4 +1,5 @@
 // Launchers of the persistent CG solve (the instances live in solve_n*.hip).
+#include <algorithm>
 #include <cstring>
 
 #include "solve_impl.h"
@@ -12,6 +13,17 @@ hipError_t solve_dispatch_n2(const SolveKArgs& a, bool mixed, int max_cols, int 
 hipError_t solve_dispatch_n3(const SolveKArgs& a, bool mixed, int max_cols, int threads, int depth, int groups,
                              size_t lds, hipStream_t s, int* occ);
 
+// The preconditioned CG's instances (pcg_n*.hip).
+#define EXX_PCG_DECL(name) \
+  hipError_t name(const SolveKArgs& a, int cols, int threads, int groups, size_t lds, hipStream_t s, int* occ)
+EXX_PCG_DECL(pcg_n1_f64);
+EXX_PCG_DECL(pcg_n2_f64);
+EXX_PCG_DECL(pcg_n3_f64);
+EXX_PCG_DECL(pcg_n1_mixed);
+EXX_PCG_DECL(pcg_n2_mixed);
+EXX_PCG_DECL(pcg_n3_mixed);
+#undef EXX_PCG_DECL
+
 // Two plane buffers, then the plane offsets of the class, with room for the
 // sweeps' look-ahead reads a few planes past the last one (their values are
 // discarded).
@@ -22,6 +34,45 @@ size_t solve_lds_bytes(const Geo& g, int max_zmax) {
 long long solve_slot_bytes(bool mixed, long long sstride) {
   const long long b = mixed ? 24 * sstride : 16 * sstride;
   return (b + 255) & ~255LL;
+}
+
+// Elements of the preconditioned CG's LDS buffers: one or two planes (mixed:
+// FP64 ones, whose FP32 views the sweeps use), the restriction's plane of the
+// sphere and two level-1 planes; or the coarse phase's three boxes where they
+// are more.
+static long long pcg_lds_elems(const Geo& g, const MgDev& M, bool mixed, int planes) {
+  const long long sweep = (mixed ? 2LL : 1LL) * planes * kLdsWX * g.lds_wy + (long long)M.rw * M.rh +
+                          2LL * M.ew * M.eh;
+  auto box = [](const int* D) { return (long long)D[0] * D[1] * D[2]; };
+  const long long e = std::max(sweep, box(M.D2) + box(M.D3) + box(M.D4));
+  return (e + 1) / 2 * 2;
+}
+
+static int pcg_ints(int zmax) { return 2 * zmax + 2 + 8; }
+
+static size_t pcg_lds_bytes(const Geo& g, const MgDev& M, int zmax, bool mixed, int planes) {
+  return (size_t)pcg_lds_elems(g, M, mixed, planes) * (mixed ? 4 : 8) +
+         (size_t)(pcg_ints(zmax) + 2 * M.Z1 + 2 + 8) * sizeof(int);
+}
+
+// Two planes where they fit the CU's 160 KB (1 KB for the kernels' static LDS),
+// one (a second barrier a plane) where only that does, else 0.
+static int pcg_planes(const Geo& g, const MgDev& M, int zmax, bool mixed) {
+  for (int planes = 2; planes >= 1; --planes)
+    if (pcg_lds_bytes(g, M, zmax, mixed, planes) + 1024 <= 160 * 1024) return planes;
+  return 0;
+}
+
+long long pcg_slot_bytes(bool mixed, long long sstride, long long c1stride, long long b2stride) {
+  // r, q and the ring of p; the mixed solve's x (FP64) and y
+  const long long b = (mixed ? 12 * sstride : 0) +
+                      (mixed ? 4 : 8) * ((2 + kPcgRing) * sstride + 3 * c1stride + 2 * b2stride);
+  return (b + 255) & ~255LL;
+}
+
+bool pcg_supported(const Geo& g, const ClassHost& C, bool mixed) {
+  return C.mg.n_c1 > 0 && C.mg.n_c1 <= 1024 && C.mg.n_c2 <= 512 && (int)C.fin_cols.size() <= 4096 &&
+         pcg_planes(g, C.mg, C.Zmax, mixed) > 0;
 }
 
 static hipError_t solve_dispatch(const SolveArgs& in, int max_cols, int max_zmax, int groups, hipStream_t s,
@@ -134,6 +185,30 @@ static hipError_t solve_dispatch(const SolveArgs& in, int max_cols, int max_zmax
   a.lds_cy = in.g.lds_cy;
   a.lds_wx = in.g.lds_wx;
   a.lds_wy = in.g.lds_wy;
+  if (in.pcg_cols > 0) {
+    a.slot_bytes = pcg_slot_bytes(in.mixed, in.sstride, in.c1stride, in.b2stride);
+    a.c1stride = in.c1stride;
+    a.b2stride = in.b2stride;
+    a.pcg_planes = pcg_planes(in.g, in.mg, max_zmax, in.mixed);
+    if (a.pcg_planes == 0) return hipErrorInvalidValue;
+    a.pcg_lds = (int)pcg_lds_elems(in.g, in.mg, in.mixed, a.pcg_planes);
+    a.pcg_ints = pcg_ints(max_zmax);
+    // 1 / diagonal of the operator on the sphere, and of the 3-point operator
+    // of each coarser grid in the scaling of P^T (see pcg_impl.h): the level's
+    // steps are 2^l, a cell holds 8^l points
+    double sum = 0.0;
+    if (a.gen) {
+      for (int m = 0; m < in.g.n_arms; ++m) sum += in.g.arm_coef[m];
+    } else {
+      for (int al = 0; al < 3; ++al) sum += in.g.inv_d2[al];
+    }
+    a.wl[0] = 1.0 / (-in.g.w2[0] * sum);
+    for (int l = 1; l < 5; ++l) a.wl[l] = 1.0 / ((double)(1 << l) * 2.0 * sum);
+    const size_t plds = pcg_lds_bytes(in.g, in.mg, max_zmax, in.mixed, a.pcg_planes);
+    auto* fn = in.mixed ? (in.g.n == 1 ? pcg_n1_mixed : in.g.n == 2 ? pcg_n2_mixed : pcg_n3_mixed)
+                        : (in.g.n == 1 ? pcg_n1_f64 : in.g.n == 2 ? pcg_n2_f64 : pcg_n3_f64);
+    return fn(a, in.pcg_cols, in.threads, groups, plds, s, occ);
+  }
   const size_t lds = solve_lds_bytes(in.g, max_zmax);
   switch (in.g.n) {
     case 1: return solve_dispatch_n1(a, in.mixed, max_cols, in.threads, in.depth, groups, lds, s, occ);
@@ -160,6 +235,18 @@ int solve_groups_per_cu(const Geo& g, int max_cols, int max_zmax, bool mixed, bo
   a.depth = depth;
   int occ = 0;
   if (solve_dispatch(a, max_cols, max_zmax, 1, nullptr, &occ) != hipSuccess) return 0;
+  return occ;
+}
+
+int pcg_groups_per_cu(const Geo& g, const ClassHost& C, bool mixed, int threads) {
+  SolveArgs a;
+  a.g = g;
+  a.mixed = mixed;
+  a.threads = threads;
+  a.pcg_cols = (int)C.fin_cols.size();
+  a.mg = C.mg;
+  int occ = 0;
+  if (solve_dispatch(a, C.n_cols, C.Zmax, 1, nullptr, &occ) != hipSuccess) return 0;
   return occ;
 }
 

@@ -156,6 +156,12 @@ struct SolveKArgs {
   const PairDev* prev_pairs;
   int n;                     // stencil half-width (origin of the class lookup maps)
   int N[3];                  // grid, for the periodic change of a pair's grid centre
+  // preconditioned CG (pcg_impl.h)
+  double wl[5];              // weights of levels 0 (the sphere) to 4
+  int pcg_lds;               // elements of the sweeps' LDS buffers (the coarse phase's boxes fit in them)
+  int pcg_ints;              // room for the sphere's plane offsets in front of level 1's
+  int pcg_planes;            // planes of the sphere in LDS (FP64 ones in the mixed solve): 2, or 1
+  long long c1stride, b2stride;   // elements of a level-1 vector and of a level-2 box in a slot
 };
 
 // Packed PE index of local offset (ox, oy, oz) in class C, or -1 off the sphere.
@@ -178,7 +184,7 @@ __device__ __forceinline__ int pe_index(const ClassDev& C, int n, int ox, int oy
 // points that come from outside the previous sphere start at zero), into x
 // for the pair's points.  Returns false when the pair starts from zero.
 template <typename TX>
-__device__ bool warm_gather(const SolveKArgs& a, const ClassDev& C, int pid, TX* x) {
+__device__ __forceinline__ bool warm_gather(const SolveKArgs& a, const ClassDev& C, int pid, TX* x) {
   if (!a.warm_store) return false;
   const int q = a.warm_map[pid];
   if (q < 0) return false;

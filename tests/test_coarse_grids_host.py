@@ -1,0 +1,22 @@
+"""The preconditioner's coarse grids (host tables) for spheres from a few points
+up, in orthorhombic, hexagonal and tilted cells and both layouts: index
+invariants of every table, under AddressSanitizer."""
+import os
+import subprocess
+
+import pytest
+
+from test_sanitize_host import CSRC, NATIVE, ROOT, SAN, _run, _sanitizers_available
+
+
+def test_coarse_grid_tables(tmp_path):
+    if not _sanitizers_available(tmp_path):
+        pytest.skip("gcc without ASan/UBSan runtime")
+    if not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"):
+        pytest.skip("HIP headers not installed")
+    exe = tmp_path / "coarse_grids"
+    subprocess.run(["g++", "-std=c++17", *SAN, "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-o", str(exe),
+                    os.path.join(NATIVE, "coarse_grids_main.cpp"), os.path.join(CSRC, "plan_geometry.cpp"),
+                    os.path.join(CSRC, "nk_stencil.cpp")], check=True)
+    _run(exe)
