@@ -38,6 +38,8 @@
 // 4 (a few thousand points) as dense boxes in LDS.
 #pragma once
 
+#include <type_traits>
+
 #include "solve_impl.h"
 
 namespace exx {
@@ -46,75 +48,99 @@ namespace exx {
 // registers (every lane's value is the same: the class of the workgroup's pair).
 struct MgU {
   int Z1, rw, rh, ew, eh;
-  int cx, cy;           // LDS plane origin (the sphere's centre)
-  int dx, dy;           // that of the restriction's plane is (cx - dx, cy - dy)
-  int e0;               // level-1 plane position of the sphere's centre
   int d2x, d2xy, e2z;   // level-2 box: row, plane, and half-width along the sweep
 };
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ MgU mg_uniform(const MgDev& M, int cx, int cy) {
+__device__ __forceinline__ MgU mg_uniform(const MgDev& M) {
   MgU u;
   u.Z1 = uniform(M.Z1);
-  u.cx = cx;
-  u.cy = cy;
-  u.dx = cx - uniform(M.rcx);
-  u.dy = cy - uniform(M.rcy);
   u.rw = uniform(M.rw);
   u.rh = uniform(M.rh);
   u.ew = uniform(M.ew);
   u.eh = uniform(M.eh);
-  u.e0 = uniform(M.ex) + 1 + u.ew * (uniform(M.ey) + 1);
   u.d2x = uniform(M.D2[0]);
   u.d2xy = uniform(M.D2[0] * M.D2[1]);
   u.e2z = uniform(M.E2[2]);
   return u;
 }
 
-// Columns of the sphere owned by a thread, t, t + NT, ... of the class's real
-// columns.  Only what the sweeps cannot recompute in an instruction or two is
-// kept: the sweeps' windows need the registers.
-template <int CPT, bool GEN>
-struct PCols {
-  int hi[CPT];              // the column's planes: -hi .. hi (hi -1: no column), or
-  int lo_[GEN ? CPT : 1];   // lo .. hi in a general cell
-  int col[CPT];             // slot within a plane
-  int xy[CPT];              // LDS plane coordinates: x + cx | (y + cy) << 16
-  // whether sweep plane z holds a point of column c (in an orthorhombic cell
-  // one comparison with a scalar), and whether c is a column at all
-  __device__ __forceinline__ bool valid(int c, int z) const {
-    if constexpr (GEN)
-      return z >= lo_[c] && z <= hi[c];
-    else
-      return abs(z) <= hi[c];
-  }
-  __device__ __forceinline__ bool has(int c) const {
-    if constexpr (GEN)
-      return lo_[c] <= hi[c];
-    else
-      return hi[c] >= 0;
-  }
+// The slot's working vectors as one buffer resource: a lane whose offset lies
+// past its end (kOob) reads zero and writes nothing (the scalar offset added to
+// it always lies within).  The sweeps mask their
+// lanes so instead of branching around the access: behind a branch the number
+// of accesses in flight is unknown and the compiler waits for all of them,
+// stores of the plane before included (mixed, 2,957 columns, one pair per CU:
+// a solve 9.3 ms against 7.7 ms with 1024 threads).
+// [buffer access]
+struct PBuf {
+  __amdgpu_buffer_rsrc_t r;
 };
-
-template <int CPT, int NT, bool GEN>
-__device__ __forceinline__ void pcg_cols(const ClassDev& C, int cx, int cy, PCols<CPT, GEN>& cl) {
-#pragma unroll
-  for (int c = 0; c < CPT; ++c) {
-    const int k = threadIdx.x + c * NT;
-    cl.hi[c] = -1;
-    if constexpr (GEN) cl.lo_[c] = 1;
-    cl.col[c] = 0;
-    cl.xy[c] = 0;
-    if (k < C.n_fin) {
-      const int4 f = C.fin_cols[k];
-      const int x = GEN ? (int)(short)(f.w & 0xffff) : f.z;
-      const int y = GEN ? (f.w >> 16) : f.w;
-      cl.col[c] = f.x;
-      if constexpr (GEN) cl.lo_[c] = f.y;
-      cl.hi[c] = GEN ? f.z : f.y;
-      cl.xy[c] = (x + cx) | ((y + cy) << 16);
-    }
-  }
+__device__ __forceinline__ PBuf pbuf(void* base, int bytes) {
+  return {__builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00020000)};
 }
+template <typename T>
+__device__ __forceinline__ T bload(const PBuf& b, unsigned voff, unsigned soff) {
+  if constexpr (sizeof(T) == 4)
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(b.r, voff, soff, 0));
+  else
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(b.r, voff, soff, 0));
+}
+template <typename T>
+__device__ __forceinline__ void bstore(const PBuf& b, unsigned voff, unsigned soff, T v) {
+  typedef unsigned v2u __attribute__((ext_vector_type(2)));
+  if constexpr (sizeof(T) == 4)
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), b.r, voff, soff, 0);
+  else
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, v), b.r, voff, soff, 0);
+}
+// [end of buffer access]
+constexpr unsigned kOob = 0x80000000u;
+
+// The general stencil, read anew from the kernel's arguments (one struct, at
+// the start of their segment): the 60 scalar registers that its FP64 constants
+// take are not there for a whole sweep, and kept ones were moved to lanes of
+// vector registers and back (321 moves per two steps of the FP64 sweep).
+// [kernel arguments]
+template <typename T>
+__device__ __forceinline__ GenStencilT<T> gen_args(const SolveKArgs&) {
+  typedef const __attribute__((address_space(4))) SolveKArgs KArgs;
+  KArgs* k = (KArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(k));
+  GenStencilT<T> g;
+  auto copy = [&](const auto& from) __attribute__((always_inline)) {
+    g.diag = from.diag;
+    g.cz = from.cz;
+    g.n_in = from.n_in;
+    g.n_tl = from.n_tl;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      g.w[q] = from.w[q];
+      g.czw[q] = from.czw[q];
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      g.in_off[i] = from.in_off[i];
+      g.in_coef[i] = from.in_coef[i];
+      g.tl_off[i] = from.tl_off[i];
+      g.tl_coef[i] = from.tl_coef[i];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) g.tl_cw[i][q] = from.tl_cw[i][q];
+    }
+  };
+  if constexpr (sizeof(T) == 4)
+    copy(k->G32);
+  else
+    copy(k->G);
+  return g;
+}
+// [end of kernel arguments]
+
+// A sweep's vectors, as byte offsets into the slot's buffer.  none: kOob before
+// the first direction, when p and q are to read zero, else 0.
+struct PVec {
+  PBuf all;
+  unsigned none, r, q, p, pn, e1, g1, g2;
+};
 
 // A value the compiler may not carry across loop steps: what is computed from
 // it (LDS addresses, a few integer instructions) is formed again where it is
@@ -126,22 +152,106 @@ __device__ __forceinline__ int fresh(int v) {
   return v;
 }
 
-#define EXX_PX(v) ((v) & 0xffff)
-#define EXX_PY(v) ((v) >> 16)
+// A column of the sphere, as a sweep step uses it.
+template <bool GEN>
+struct PCol {
+  int hi, lo;   // its planes: -hi .. hi (no column: hi < 0), in a general cell lo .. hi
+  int col;      // slot within a plane
+  int low;      // LDS plane position, less the NS rows that the stencil reaches up
+  // whether sweep plane z holds a point of it (in an orthorhombic cell one
+  // comparison with a scalar)
+  __device__ __forceinline__ bool valid(int z) const {
+    if constexpr (GEN)
+      return z >= lo && z <= hi;
+    else
+      return abs(z) <= hi;
+  }
+  __device__ __forceinline__ bool has() const { return GEN ? lo <= hi : hi >= 0; }
+  // whether a plane from z - d to z + d holds one (no column: no plane, or none that counts)
+  __device__ __forceinline__ bool near(int z, int d) const {
+    if constexpr (GEN)
+      return z + d >= lo && z - d <= hi;
+    else
+      return abs(z) <= hi + d;
+  }
+};
+
+// Columns of the sphere owned by a thread, t, t + NT, ... of the class's real
+// columns.  Only what the sweeps cannot recompute in a few instructions is
+// kept: the sweeps' windows need the registers.  PK (FP64, whose windows take
+// twice the registers): a column's plane slot, height and position in one
+// register, taken apart in each step.
+constexpr int kPkCol = 12, kPkLow = 13;   // bits; the rest: the height + 1
+template <int CPT, bool GEN, bool PK>
+struct PCols {
+  int a[CPT];                          // PK: packed; else the plane slot
+  int h[PK && !GEN ? 1 : CPT];         // hi, in a general cell hi & 0xffff | lo << 16
+  int p[PK ? 1 : CPT];                 // low
+  unsigned re[CPT];   // position in the restriction's plane | in the level-1 plane << 16 | parities << 30
+  __device__ __forceinline__ void put(int c, int hi, int lo, int col, int low) {
+    if constexpr (PK)
+      a[c] = (int)((unsigned)col | (unsigned)low << kPkCol | (GEN ? 0u : (unsigned)(hi + 1) << (kPkCol + kPkLow)));
+    else
+      a[c] = col;
+    if constexpr (GEN)
+      h[c] = (hi & 0xffff) | (int)((unsigned)lo << 16);
+    else if constexpr (!PK)
+      h[c] = hi;
+    if constexpr (!PK) p[c] = low;
+  }
+  __device__ __forceinline__ PCol<GEN> get(int c) const {
+    PCol<GEN> k;
+    const int v = PK ? fresh(a[c]) : a[c];
+    k.col = PK ? v & ((1 << kPkCol) - 1) : v;
+    k.low = PK ? (v >> kPkCol) & ((1 << kPkLow) - 1) : fresh(p[PK ? 0 : c]);
+    if constexpr (GEN) {
+      const int w = fresh(h[c]);
+      k.hi = (int)(short)(w & 0xffff);
+      k.lo = w >> 16;
+    } else {
+      k.hi = PK ? (int)((unsigned)v >> (kPkCol + kPkLow)) - 1 : h[PK ? 0 : c];
+      k.lo = 0;
+    }
+    return k;
+  }
+  __device__ __forceinline__ bool valid(int c, int z) const { return get(c).valid(z); }
+  __device__ __forceinline__ bool has(int c) const { return get(c).has(); }
+};
+
+// Byte offset of the column's point in a plane, or kOob.
+template <typename T, bool GEN>
+__device__ __forceinline__ unsigned pcg_off(const PCol<GEN>& k, bool in) {
+  return in ? (unsigned)k.col * (unsigned)sizeof(T) : kOob;
+}
+
+// (No column: positions that stay zero, where the sweeps may write zeros.)
+template <int NS, int CPT, int NT, bool GEN, bool PK>
+__device__ __forceinline__ void pcg_cols(const ClassDev& C, int cx, int cy, PCols<CPT, GEN, PK>& cl) {
+  const MgDev& M = C.mg;
+#pragma unroll
+  for (int c = 0; c < CPT; ++c) {
+    const int k = threadIdx.x + c * NT;
+    cl.put(c, -1, 1, 0, 0);
+    cl.re[c] = 0;
+    if (k < C.n_fin) {
+      const int4 f = C.fin_cols[k];
+      const int x = GEN ? (int)(short)(f.w & 0xffff) : f.z;
+      const int y = GEN ? (f.w >> 16) : f.w;
+      cl.put(c, GEN ? f.z : f.y, GEN ? f.y : 0, f.x, (x + cx) + kLdsWX * (y + cy - NS));
+      const int r1 = (x + M.rcx) + M.rw * (y + M.rcy);
+      const int e = ((x >> 1) + M.ex + 1) + M.ew * ((y >> 1) + M.ey + 1);
+      cl.re[c] = (unsigned)r1 | (unsigned)e << 16 | (unsigned)(x & 1) << 30 | (unsigned)(y & 1) << 31;
+    }
+  }
+}
+
 #define EXX_PVALID(c, zz) cl.valid(c, zz)
 #define EXX_PHAS(c) cl.has(c)
-#define EXX_PIDX(c, base) ((base) + (unsigned)cl.col[c])
-// LDS plane position, and the one in the restriction's plane
-__device__ __forceinline__ int pcg_pos(int xy) {
-  xy = fresh(xy);
-  return EXX_PX(xy) + kLdsWX * EXX_PY(xy);
-}
-__device__ __forceinline__ int pcg_pos1(const MgU& M, int xy) {
-  xy = fresh(xy);
-  return (EXX_PX(xy) - M.dx) + M.rw * (EXX_PY(xy) - M.dy);
-}
-#define EXX_PPOS(c) pcg_pos(cl.xy[c])
-#define EXX_PR1(c) pcg_pos1(M, cl.xy[c])
+#define EXX_PIDX(c, base) ((base) + (unsigned)cl.get(c).col)
+// LDS plane position (from the stencil's first row on: its offsets are all
+// positive and go into the instructions), and the one in the restriction's plane
+#define EXX_PPOS(c) (cl.get(c).low + NS * kLdsWX)
+#define EXX_PR1(c) (fresh((int)cl.re[c]) & 0xffff)
 
 // First slots of the N planes z, z + 1, ... of a sweep step, in scalar
 // registers.  Each step takes one new one from LDS and shifts: read where they
@@ -164,14 +274,23 @@ struct PBase {
   }
 };
 
-// A thread's level-1 columns (CC of them) and its level-2 column.
+// A thread's level-1 columns (CC of them) and its level-2 column, two 16-bit
+// values to a register.
 template <int CC>
 struct PCoarse {
-  int lo[CC], hi[CC];
-  int r1[CC];       // position of the column's centre in the staged plane of the sphere
-  int ep[CC];       // position in the staged level-1 plane
-  int lo2, hi2, r2; // level-2 column: its interval and centre in the staged level-1 plane
-  int b2;           // its position in a plane of the level-2 box
+  int iv[CC];     // planes: lo | hi << 16
+  int ps[CC];     // position of the column's centre in the staged plane of the sphere | in the staged level-1 plane << 16
+  int iv2, ps2;   // level-2 column: planes; centre in the staged level-1 plane | place in a plane of the level-2 box << 16
+};
+__device__ __forceinline__ int pack16(int a, int b) { return (a & 0xffff) | (int)((unsigned)b << 16); }
+// the halves, formed again at each use; lower signed
+struct PHalves {
+  int a, b;
+  __device__ __forceinline__ explicit PHalves(int v) {
+    const int w = fresh(v);
+    a = (int)(short)(w & 0xffff);
+    b = w >> 16;
+  }
 };
 
 template <int CC, int NT>
@@ -180,29 +299,22 @@ __device__ __forceinline__ void pcg_coarse_cols(const ClassDev& C, PCoarse<CC>& 
   const int t = threadIdx.x;
 #pragma unroll
   for (int u = 0; u < CC; ++u) {
-    k.lo[u] = 1;
-    k.hi[u] = 0;
-    k.r1[u] = M.rw + 1;
-    k.ep[u] = 0;
+    k.iv[u] = pack16(1, 0);
+    k.ps[u] = M.rw + 1;
     const int i = t + u * NT;
     if (i < M.n_c1) {
       const int4 f = M.c1cols[i];
-      k.lo[u] = f.z;
-      k.hi[u] = f.w;
-      k.r1[u] = (2 * f.x + M.rcx) + M.rw * (2 * f.y + M.rcy);
-      k.ep[u] = (f.x + M.ex + 1) + M.ew * (f.y + M.ey + 1);
+      k.iv[u] = pack16(f.z, f.w);
+      k.ps[u] = pack16((2 * f.x + M.rcx) + M.rw * (2 * f.y + M.rcy), (f.x + M.ex + 1) + M.ew * (f.y + M.ey + 1));
     }
   }
-  k.lo2 = 1;
-  k.hi2 = 0;
-  k.r2 = M.ew + 1;
-  k.b2 = 0;
+  k.iv2 = pack16(1, 0);
+  k.ps2 = M.ew + 1;
   if (t < M.n_c2) {
     const int4 f = M.c2cols[t];
-    k.lo2 = f.z;
-    k.hi2 = f.w;
-    k.r2 = (2 * f.x + M.ex + 1) + M.ew * (2 * f.y + M.ey + 1);
-    k.b2 = (f.x + M.E2[0] + 1) + M.D2[0] * (f.y + M.E2[1] + 1);
+    k.iv2 = pack16(f.z, f.w);
+    k.ps2 = pack16((2 * f.x + M.ex + 1) + M.ew * (2 * f.y + M.ey + 1),
+                   (f.x + M.E2[0] + 1) + M.D2[0] * (f.y + M.E2[1] + 1));
   }
 }
 
@@ -217,11 +329,10 @@ __device__ __forceinline__ T restrict9(const T* b, int w) {
 // The in-plane part of the interpolation at a fine column (x, y): the average
 // of the level-1 values at (x >> 1, x + 1 >> 1) x (y >> 1, y + 1 >> 1).
 template <typename T>
-__device__ __forceinline__ T prolong4(const T* E, int xy, const MgU& M) {
-  xy = fresh(xy);
-  const int x = EXX_PX(xy) - M.cx, y = EXX_PY(xy) - M.cy;
-  const T* b = E + ((x >> 1) + M.ew * (y >> 1) + M.e0);
-  const int dx = x & 1, dy = (y & 1) ? M.ew : 0;
+__device__ __forceinline__ T prolong4(const T* E, unsigned re, const MgU& M) {
+  re = (unsigned)fresh((int)re);
+  const T* b = E + ((re >> 16) & 0x3fff);
+  const int dx = (re >> 30) & 1, dy = (re >> 31) ? M.ew : 0;
   return (T)0.25 * ((b[0] + b[dx]) + (b[dy] + b[dx + dy]));
 }
 
@@ -248,47 +359,58 @@ struct PLds {
   T *R1, *R2, *E;
 };
 
-// The restriction streamed with a pass B.  `done` is called with the sweep
-// plane z just finished (before its barrier's successor): column sums in acc.
+// The restriction streamed with a sweep: level-2 sums of the level-1 columns.
 template <int CC, typename T>
 struct PRestrict {
   T acc2[CC];
 };
 
-// Level-1 and level-2 part of one sweep step (after its barrier).  z is the
-// step's centre plane; the combination staged at the odd plane z - 1 completes
-// level-1 plane (z - 2) / 2.
+// Level-1 part of an even sweep step (after its barrier), level-2 part of an
+// odd one.  z is the step's centre plane; the combination staged at the odd
+// plane z - 1 completes level-1 plane (z - 2) / 2.  c1 and b2: byte offsets of
+// the results in buffer B.
 template <int CC, int NT, typename T>
-__device__ __forceinline__ void pcg_restrict_step(const MgU& M, const PCoarse<CC>& k, const PLds<T>& L,
-                                                  const int* cst, int z, PRestrict<CC, T>& R, T* c1, T* b2) {
-  if (!(z & 1)) {
-    const int kz = (z - 2) >> 1;
-    if (kz >= -M.Z1 && kz <= M.Z1 + 1) {
-      const bool fin = kz & 1;   // completes a level-2 plane
-      const unsigned base = kz <= M.Z1 ? plane_base(cst, kz + M.Z1) : 0u;
+__device__ __forceinline__ void pcg_restrict_even(const MgU& M, const PCoarse<CC>& k, const PLds<T>& L,
+                                                  const int* cst, int z, PRestrict<CC, T>& R, const PBuf& B,
+                                                  unsigned c1) {
+  const int kz = (z - 2) >> 1;
+  const bool fin = kz & 1;   // completes a level-2 plane
+  const unsigned base = PBase<1>::at(cst, M.Z1, kz) * sizeof(T);
 #pragma unroll
-      for (int u = 0; u < CC; ++u) {
-        if (u > 0 && k.lo[u] > k.hi[u]) continue;
-        T v = 0;
-        if (kz >= k.lo[u] && kz <= k.hi[u]) {
-          v = restrict9<T>(L.R1 + fresh(k.r1[u]), M.rw);
-          gstore(c1, base + (unsigned)(threadIdx.x + u * NT), v);
-        }
-        if (fin) {
-          if (k.lo[u] <= k.hi[u]) L.R2[fresh(k.ep[u])] = R.acc2[u] + (T)0.5 * v;
-          R.acc2[u] = (T)0.5 * v;
-        } else {
-          R.acc2[u] += v;
-        }
-      }
-    }
-  } else {
-    const int kz = (z - 3) >> 1;   // level-1 plane of the previous step
-    if ((kz & 1) && kz >= -M.Z1 && kz <= M.Z1 + 1) {
-      const int k2 = (kz - 1) >> 1;
-      if (k2 >= k.lo2 && k2 <= k.hi2) b2[k.b2 + M.d2xy * (k2 + M.e2z + 1)] = restrict9<T>(L.R2 + fresh(k.r2), M.ew);
+  for (int u = 0; u < CC; ++u) {
+    const PHalves iv(k.iv[u]), ps(k.ps[u]);
+    const bool in = kz >= iv.a && kz <= iv.b;
+    T v = 0;
+    if (in) v = restrict9<T>(L.R1 + ps.a, M.rw);
+    bstore<T>(B, in ? (threadIdx.x + u * NT) * (unsigned)sizeof(T) : kOob, c1 + base, v);
+    if (fin) {
+      if (iv.a <= iv.b) L.R2[ps.b] = R.acc2[u] + (T)0.5 * v;
+      R.acc2[u] = (T)0.5 * v;
+    } else {
+      R.acc2[u] += v;
     }
   }
+}
+template <int CC, typename T>
+__device__ __forceinline__ void pcg_restrict_odd(const MgU& M, const PCoarse<CC>& k, const PLds<T>& L, int z,
+                                                 const PBuf& B, unsigned b2) {
+  const int kz = (z - 3) >> 1;   // level-1 plane of the previous step
+  const int k2 = (kz - 1) >> 1;
+  const PHalves iv(k.iv2), ps(k.ps2);
+  const bool in = (kz & 1) && k2 >= iv.a && k2 <= iv.b;
+  const unsigned plane = (unsigned)uniform(M.d2xy * min(max(k2 + M.e2z + 1, 0), 2 * M.e2z + 2));
+  T v = 0;
+  if (in) v = restrict9<T>(L.R2 + ps.a, M.ew);
+  bstore<T>(B, in ? (unsigned)ps.b * (unsigned)sizeof(T) : kOob, b2 + plane * (unsigned)sizeof(T), v);
+}
+template <int CC, int NT, typename T>
+__device__ __forceinline__ void pcg_restrict_step(const MgU& M, const PCoarse<CC>& k, const PLds<T>& L,
+                                                  const int* cst, int z, PRestrict<CC, T>& R, const PBuf& B,
+                                                  unsigned c1, unsigned b2) {
+  if (z & 1)
+    pcg_restrict_odd<CC, T>(M, k, L, z, B, b2);
+  else
+    pcg_restrict_even<CC, NT, T>(M, k, L, cst, z, R, B, c1);
 }
 
 // Last sweep step that the streamed restriction needs.
@@ -307,14 +429,14 @@ struct PSums {
 // The sweep, window form (orthorhombic cells; general cells without arms
 // leaving the sweep plane): plane zc enters, plane z = zc - NS is its windows'
 // centre.  r, p and q of the next plane are loaded between the use of this
-// plane's and the barrier, so one register set holds them.  pn receives the
-// new p.  first: p = w_0 r + P e, nothing else read.
-template <int NS, int CPT, int NT, bool GEN, int CC, typename T>
+// plane's and the barrier, so one register set holds them.  Steps go in pairs
+// (an even plane, an odd one), so that what a plane's parity decides is decided
+// at compile time.  Before the first direction alpha, beta, p and q are zero.
+template <int NS, int CPT, int NT, bool GEN, int CC, typename T, bool PK>
 __device__ __forceinline__ PSums pcg_sweep_w(const StencilT<T>& S, const GenStencilT<T>& G, const MgU& M,
-                                             const PCols<CPT, GEN>& cl, const PCoarse<CC>& ck, const int* pst,
-                                             const int* cst, int Zmax, T* r, T* q, const T* p, T* pn,
-                                             const T* __restrict__ e1, T w0, T alpha, T beta, bool first,
-                                             T* g1, T* g2, const PLds<T>& L) {
+                                             const PCols<CPT, GEN, PK>& cl, const PCoarse<CC>& ck, const int* pst,
+                                             const int* cst, int Zmax, const PVec& V, T w0, T alpha, T beta,
+                                             const PLds<T>& L) {
   T win[CPT][2 * NS + 1];
   T lr[CPT], lp[CPT], lq[CPT], Bc[CPT], acc[CPT], ev[CC];
   PRestrict<CC, T> R;
@@ -323,6 +445,7 @@ __device__ __forceinline__ PSums pcg_sweep_w(const StencilT<T>& S, const GenSten
   // the next (odd) step interpolates
   const int z0 = -Zmax - 2 + (Zmax & 1);
   const int zl = pcg_last_step(M, Zmax) + NS;
+  PBase<NS + 2> pb(pst, Zmax, z0 - NS);   // planes zc - NS .. zc + 1
 #pragma unroll
   for (int u = 0; u < CC; ++u) R.acc2[u] = 0;
 #pragma unroll
@@ -331,76 +454,76 @@ __device__ __forceinline__ PSums pcg_sweep_w(const StencilT<T>& S, const GenSten
 #pragma unroll
     for (int k = 0; k < 2 * NS + 1; ++k) win[c][k] = 0;
   }
-  auto load_e = [&](int kz) {
-    const unsigned base = PBase<1>::at(cst, M.Z1, kz) + threadIdx.x;
+  auto load_e = [&](int kz) {   // a level-1 plane of the correction
+    const unsigned base = V.e1 + PBase<1>::at(cst, M.Z1, kz) * (unsigned)sizeof(T);
 #pragma unroll
     for (int u = 0; u < CC; ++u) {
-      ev[u] = 0;
-      if (kz >= ck.lo[u] && kz <= ck.hi[u]) ev[u] = gload(e1, base + u * NT);
+      const PHalves iv(ck.iv[u]);
+      ev[u] = bload<T>(V.all, kz >= iv.a && kz <= iv.b ? (threadIdx.x + u * NT) * (unsigned)sizeof(T) : kOob, base);
     }
   };
   load_e((z0 + 2) >> 1);
-  PBase<NS + 2> pb(pst, Zmax, z0 - NS);   // planes zc - NS .. zc + 1
-  for (int zc = z0; zc <= zl; ++zc) {
+  auto body = [&](auto odd, int zc) __attribute__((always_inline)) {
+    constexpr bool ODD = decltype(odd)::value, ZODD = ODD != (bool)(NS & 1);
     const int z = zc - NS;
+    // byte offsets of planes zc - NS .. of a vector: V.x + at(k)
+    auto at = [&](int k) __attribute__((always_inline)) { return pb.b[k] * (unsigned)sizeof(T); };
+    if constexpr (ODD) load_e((zc + 3) >> 1);
+    T* pl = L.pl0 + ((z & 1) ? L.plane : 0);
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
       T pe = Bc[c];
-      if (zc & 1) {
-        const T Bn = EXX_PHAS(c) ? prolong4<T>(L.E, cl.xy[c], M) : (T)0;
+      if constexpr (ODD) {
+        const T Bn = prolong4<T>(L.E, cl.re[c], M);
         pe = (T)0.5 * (pe + Bn);
         Bc[c] = Bn;
       }
+      const PCol<GEN> k = cl.get(c);
 #pragma unroll
-      for (int k = 0; k < 2 * NS; ++k) win[c][k] = win[c][k + 1];
-      T v = 0;
-      if (EXX_PVALID(c, zc)) {
-        const unsigned idx = EXX_PIDX(c, pb.b[NS]);
-        T rn = lr[c];
-        if (!first) {
-          rn -= alpha * lq[c];
-          gstore(r, idx, rn);
-        }
-        v = w0 * rn + pe;
-        if (!first) v += beta * lp[c];
-        gstore(pn, idx, v);
-        s.rr += (double)rn * (double)rn;
-      }
+      for (int m = 0; m < 2 * NS; ++m) win[c][m] = win[c][m + 1];
+      const bool in = k.valid(zc);
+      const unsigned vo = pcg_off<T>(k, in);
+      const T rn = lr[c] - alpha * lq[c];
+      T v = (w0 * rn + pe) + beta * lp[c];
+      v = in ? v : (T)0;
+      bstore<T>(V.all, vo, V.r + at(NS), rn);
+      bstore<T>(V.all, vo, V.pn + at(NS), v);
+      s.rr += (double)rn * (double)rn;
       win[c][2 * NS] = v;
-      lr[c] = lp[c] = lq[c] = 0;
-      if (EXX_PVALID(c, zc + 1)) {
-        const unsigned idx = EXX_PIDX(c, pb.b[NS + 1]);
-        lr[c] = gload(r, idx);
-        if (!first) {
-          lp[c] = gload(p, idx);
-          lq[c] = gload(q, idx);
-        }
-      }
+      pl[k.low + NS * kLdsWX] = win[c][NS];
     }
-    T* pl = L.pl0 + ((z & 1) ? L.plane : 0);
-#pragma unroll
-    for (int c = 0; c < CPT; ++c)
-      if (EXX_PHAS(c)) pl[EXX_PPOS(c)] = win[c][NS];
-    if (!(zc & 1)) {   // level-1 plane (zc + 2) / 2, interpolated in the next step
-#pragma unroll
-      for (int u = 0; u < CC; ++u)
-        if (ck.lo[u] <= ck.hi[u]) L.E[fresh(ck.ep[u])] = ev[u];
-    }
-    __syncthreads();
-    if (zc & 1) load_e((zc + 3) >> 1);
-    if (z >= -Zmax) pcg_restrict_step<CC, NT, T>(M, ck, L, cst, z, R, g1, g2);
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
-      T qv = 0;
-      if (EXX_PVALID(c, z)) {
-        qv = pcg_apply<NS, GEN, T>(S, G, win[c][NS], pl, EXX_PPOS(c), win[c]);
-        gstore(q, EXX_PIDX(c, pb.b[0]), qv);
-        s.pq += (double)win[c][NS] * (double)qv;
-        s.qq += (double)qv * (double)qv;
+      const PCol<GEN> k = cl.get(c);
+      const unsigned vo = pcg_off<T>(k, k.valid(zc + 1));
+      lr[c] = bload<T>(V.all, vo, V.r + at(NS + 1));
+      lp[c] = bload<T>(V.all, vo | V.none, V.p + at(NS + 1));
+      lq[c] = bload<T>(V.all, vo | V.none, V.q + at(NS + 1));
+    }
+    if constexpr (!ODD) {   // level-1 plane (zc + 2) / 2, interpolated in the next step
+#pragma unroll
+      for (int u = 0; u < CC; ++u) {
+        const PHalves iv(ck.iv[u]);
+        if (iv.a <= iv.b) L.E[PHalves(ck.ps[u]).b] = ev[u];
       }
-      if (z & 1) {
+    }
+    __syncthreads();
+    if constexpr (ZODD)
+      pcg_restrict_odd<CC, T>(M, ck, L, z, V.all, V.g2);
+    else
+      pcg_restrict_even<CC, NT, T>(M, ck, L, cst, z, R, V.all, V.g1);
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) {
+      const PCol<GEN> k = cl.get(c);
+      const bool in = k.valid(z);
+      T qv = 0;
+      if (in) qv = pcg_apply<NS, GEN, T>(S, G, win[c][NS], pl, k.low + NS * kLdsWX, win[c]);
+      bstore<T>(V.all, pcg_off<T>(k, in), V.q + at(0), qv);
+      s.pq += (double)win[c][NS] * (double)qv;
+      s.qq += (double)qv * (double)qv;
+      if constexpr (ZODD) {
         const T h = (T)0.5 * qv;
-        if (EXX_PHAS(c)) L.R1[EXX_PR1(c)] = acc[c] + h;
+        L.R1[EXX_PR1(c)] = acc[c] + h;
         acc[c] = h;
       } else {
         acc[c] += qv;
@@ -408,6 +531,10 @@ __device__ __forceinline__ PSums pcg_sweep_w(const StencilT<T>& S, const GenSten
     }
     pb.next(pst, Zmax, zc - NS);
     if (L.plane == 0) __syncthreads();   // one plane: its readers are done
+  };
+  for (int zc = z0; zc <= zl; zc += 2) {
+    body(std::false_type(), zc);
+    body(std::true_type(), zc + 1);
   }
   __syncthreads();
   return s;
@@ -417,11 +544,10 @@ __device__ __forceinline__ PSums pcg_sweep_w(const StencilT<T>& S, const GenSten
 // from p, whose plane zc is staged with the new direction's plane z.  Five and a
 // half accesses per point for a second stencil: the choice where the registers
 // hold both windows (FP32 with 512 or 768 threads).
-template <int NS, int CPT, int NT, bool GEN, int CC, typename T>
+template <int NS, int CPT, int NT, bool GEN, int CC, typename T, bool PK>
 __device__ __forceinline__ PSums pcg_sweep_rq(const StencilT<T>& S, const GenStencilT<T>& G, const MgU& M,
-                                              const PCols<CPT, GEN>& cl, const PCoarse<CC>& ck, const int* pst,
-                                              const int* cst, int Zmax, T* r, const T* p, T* pn,
-                                              const T* __restrict__ e1, T w0, T alpha, T beta, bool first, T* g1, T* g2,
+                                              const PCols<CPT, GEN, PK>& cl, const PCoarse<CC>& ck, const int* pst,
+                                              const int* cst, int Zmax, const PVec& V, T w0, T alpha, T beta,
                                               const PLds<T>& L) {
   T wo[CPT][2 * NS + 1], wn[CPT][2 * NS + 1];   // windows of p around zc and of the new p around z
   T lr[CPT], lp[CPT], pe[CPT], Bc[CPT], acc[CPT], ev[CC];
@@ -432,29 +558,36 @@ __device__ __forceinline__ PSums pcg_sweep_rq(const StencilT<T>& S, const GenSte
   PBase<2 * NS + 2> pb(pst, Zmax, z0 - NS);   // planes zc - NS .. zc + NS + 1
 #pragma unroll
   for (int u = 0; u < CC; ++u) R.acc2[u] = 0;
+  auto off = [&](int c, int zz) __attribute__((always_inline)) {
+    const PCol<GEN> k = cl.get(c);
+    return pcg_off<T>(k, k.valid(zz));
+  };
 #pragma unroll
   for (int c = 0; c < CPT; ++c) {
     lr[c] = Bc[c] = acc[c] = 0;
 #pragma unroll
     for (int k = 0; k < 2 * NS + 1; ++k) {
       wn[c][k] = 0;
-      const int zz = z0 - NS - 1 + k;
       wo[c][k] = 0;
-      if (k > NS && !first && EXX_PVALID(c, zz)) wo[c][k] = gload(p, EXX_PIDX(c, pb.b[k > 0 ? k - 1 : 0]));
+      if (k > NS) wo[c][k] = bload<T>(V.all, off(c, z0 - NS - 1 + k) | V.none, V.p + pb.b[k > 0 ? k - 1 : 0] * (unsigned)sizeof(T));
     }
-    lp[c] = !first && EXX_PVALID(c, z0 + NS) ? gload(p, EXX_PIDX(c, pb.b[2 * NS])) : (T)0;
+    lp[c] = bload<T>(V.all, off(c, z0 + NS) | V.none, V.p + pb.b[2 * NS] * (unsigned)sizeof(T));
   }
-  auto load_e = [&](int kz) {
-    const unsigned base = PBase<1>::at(cst, M.Z1, kz) + threadIdx.x;
+  auto load_e = [&](int kz) {   // a level-1 plane of the correction
+    const unsigned base = V.e1 + PBase<1>::at(cst, M.Z1, kz) * (unsigned)sizeof(T);
 #pragma unroll
     for (int u = 0; u < CC; ++u) {
-      ev[u] = 0;
-      if (kz >= ck.lo[u] && kz <= ck.hi[u]) ev[u] = gload(e1, base + u * NT);
+      const PHalves iv(ck.iv[u]);
+      ev[u] = bload<T>(V.all, kz >= iv.a && kz <= iv.b ? (threadIdx.x + u * NT) * (unsigned)sizeof(T) : kOob, base);
     }
   };
   load_e((z0 + 2) >> 1);
-  for (int zc = z0; zc <= zl; ++zc) {
+  auto body = [&](auto odd, int zc) __attribute__((always_inline)) {
+    constexpr bool ODD = decltype(odd)::value, ZODD = ODD != (bool)(NS & 1);
     const int z = zc - NS;
+    // byte offsets of planes zc - NS .. of a vector: V.x + at(k)
+    auto at = [&](int k) __attribute__((always_inline)) { return pb.b[k] * (unsigned)sizeof(T); };
+    if constexpr (ODD) load_e((zc + 3) >> 1);
     T* pl = L.pl0 + ((zc & 1) ? L.plane : 0);
     T* po = pl + L.old;
 #pragma unroll
@@ -465,54 +598,51 @@ __device__ __forceinline__ PSums pcg_sweep_rq(const StencilT<T>& S, const GenSte
         wn[c][k] = wn[c][k + 1];
       }
       wo[c][2 * NS] = lp[c];
-      lp[c] = 0;
-      if (!first && EXX_PVALID(c, zc + NS + 1)) lp[c] = gload(p, EXX_PIDX(c, pb.b[2 * NS + 1]));
-      if (EXX_PHAS(c)) {
-        const int pos = EXX_PPOS(c);
-        po[pos] = wo[c][NS];
-        pl[pos] = wn[c][NS];
-      }
+      const int pos = EXX_PPOS(c);
+      po[pos] = wo[c][NS];
+      pl[pos] = wn[c][NS];
       pe[c] = Bc[c];
-      if (zc & 1) {
-        const T Bn = EXX_PHAS(c) ? prolong4<T>(L.E, cl.xy[c], M) : (T)0;
+      if constexpr (ODD) {
+        const T Bn = prolong4<T>(L.E, cl.re[c], M);
         pe[c] = (T)0.5 * (pe[c] + Bn);
         Bc[c] = Bn;
       }
     }
-    if (!(zc & 1)) {   // level-1 plane (zc + 2) / 2, interpolated in the next step
 #pragma unroll
-      for (int u = 0; u < CC; ++u)
-        if (ck.lo[u] <= ck.hi[u]) L.E[fresh(ck.ep[u])] = ev[u];
+    for (int c = 0; c < CPT; ++c) lp[c] = bload<T>(V.all, off(c, zc + NS + 1) | V.none, V.p + at(2 * NS + 1));
+    if constexpr (!ODD) {   // level-1 plane (zc + 2) / 2, interpolated in the next step
+#pragma unroll
+      for (int u = 0; u < CC; ++u) {
+        const PHalves iv(ck.iv[u]);
+        if (iv.a <= iv.b) L.E[PHalves(ck.ps[u]).b] = ev[u];
+      }
     }
     __syncthreads();
-    if (zc & 1) load_e((zc + 3) >> 1);
-    if (z >= -Zmax) pcg_restrict_step<CC, NT, T>(M, ck, L, cst, z, R, g1, g2);
+    if constexpr (ZODD)
+      pcg_restrict_odd<CC, T>(M, ck, L, z, V.all, V.g2);
+    else
+      pcg_restrict_even<CC, NT, T>(M, ck, L, cst, z, R, V.all, V.g1);
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
-      T v = 0;
-      if (EXX_PVALID(c, zc)) {
-        const unsigned idx = EXX_PIDX(c, pb.b[NS]);
-        T rn = lr[c];
-        if (!first) {
-          rn -= alpha * pcg_apply<NS, GEN, T>(S, G, wo[c][NS], po, EXX_PPOS(c), wo[c]);
-          gstore(r, idx, rn);
-        }
-        v = w0 * rn + pe[c];
-        if (!first) v += beta * wo[c][NS];
-        gstore(pn, idx, v);
-        s.rr += (double)rn * (double)rn;
-      }
+      const PCol<GEN> k = cl.get(c);
+      const bool in = k.valid(zc);
+      T qo = 0;
+      if (in) qo = pcg_apply<NS, GEN, T>(S, G, wo[c][NS], po, k.low + NS * kLdsWX, wo[c]);
+      const T rn = lr[c] - alpha * qo;
+      T v = (w0 * rn + pe[c]) + beta * wo[c][NS];
+      v = in ? v : (T)0;
+      bstore<T>(V.all, pcg_off<T>(k, in), V.r + at(NS), rn);
+      bstore<T>(V.all, pcg_off<T>(k, in), V.pn + at(NS), v);
+      s.rr += (double)rn * (double)rn;
       wn[c][2 * NS] = v;
-      lr[c] = EXX_PVALID(c, zc + 1) ? gload(r, EXX_PIDX(c, pb.b[NS + 1])) : (T)0;
+      lr[c] = bload<T>(V.all, pcg_off<T>(k, k.valid(zc + 1)), V.r + at(NS + 1));
       T qv = 0;
-      if (EXX_PVALID(c, z)) {
-        qv = pcg_apply<NS, GEN, T>(S, G, wn[c][NS], pl, EXX_PPOS(c), wn[c]);
-        s.pq += (double)wn[c][NS] * (double)qv;
-        s.qq += (double)qv * (double)qv;
-      }
-      if (z & 1) {
+      if (k.valid(z)) qv = pcg_apply<NS, GEN, T>(S, G, wn[c][NS], pl, k.low + NS * kLdsWX, wn[c]);
+      s.pq += (double)wn[c][NS] * (double)qv;
+      s.qq += (double)qv * (double)qv;
+      if constexpr (ZODD) {
         const T h = (T)0.5 * qv;
-        if (EXX_PHAS(c)) L.R1[EXX_PR1(c)] = acc[c] + h;
+        L.R1[EXX_PR1(c)] = acc[c] + h;
         acc[c] = h;
       } else {
         acc[c] += qv;
@@ -520,25 +650,62 @@ __device__ __forceinline__ PSums pcg_sweep_rq(const StencilT<T>& S, const GenSte
     }
     pb.next(pst, Zmax, zc - NS);
     if (L.plane == 0) __syncthreads();   // one plane: its readers are done
+  };
+  for (int zc = z0; zc <= zl; zc += 2) {
+    body(std::false_type(), zc);
+    body(std::true_type(), zc + 1);
   }
   __syncthreads();
   return s;
 }
 
+// tl_scatter with the arms of a stencil read anew (constant indices only: the
+// copy is then never in memory).
+template <int NS, typename T>
+__device__ __forceinline__ void pcg_scatter(const GenStencilT<T>& S, T v, bool point, const T* pl, int pos, T* acc) {
+  if (point) {
+    T s = S.diag * v;
+    const T* bp = pl + pos;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      if (k >= S.n_in) break;
+      const int off = S.in_off[k];
+      T t = 0;
+#pragma unroll
+      for (int q = 1; q <= NS; ++q) t += S.w[q] * (bp[q * off] + bp[-q * off]);
+      s += S.in_coef[k] * t;
+    }
+    acc[NS] += s;
+  }
+#pragma unroll
+  for (int q = 1; q <= NS; ++q) {
+    const T t = S.czw[q] * v;
+    acc[NS - q] += t;
+    acc[NS + q] += t;
+  }
+  gen_tilted<NS, NS, T>(S, pl, pos, acc);
+}
+
 // The same with arms leaving the sweep plane: a plane of the new p is staged
 // as it enters and scattered into the partial sums of its columns' points; the
-// point n planes behind completes (see cg_pass_a_tl).
-template <int NS, int CPT, int NT, int CC, typename T, bool GEN = true>
-__device__ __forceinline__ PSums pcg_sweep_tl(const GenStencilT<T>& G, const MgU& M, const PCols<CPT, GEN>& cl,
-                                              const PCoarse<CC>& ck, const int* pst, const int* cst, int Zmax,
-                                              T* r, T* q, const T* p, T* pn, const T* __restrict__ e1, T w0, T alpha,
-                                              T beta, bool first, T* g1, T* g2, const PLds<T>& L) {
-  T pd[CPT][NS + 1], sum[CPT][2 * NS + 1];
+// point n planes behind completes (see cg_pass_a_tl).  p.q is summed as the
+// planes enter, A being symmetric: p times its own plane's part and twice what
+// the planes before have left in its sum, so no window of p is kept.
+template <int NS, int CPT, int NT, int CC, typename T, bool GEN = true, bool PK = false>
+__device__ __forceinline__ PSums pcg_sweep_tl(const SolveKArgs& a, const MgU& M,
+                                              const PCols<CPT, GEN, PK>& cl, const PCoarse<CC>& ck, const int* pst,
+                                              const int* cst, int Zmax, const PVec& V, T w0, T alpha, T beta,
+                                              const PLds<T>& L) {
+  T sum[CPT][2 * NS + 1], pv[CPT];   // partial sums of planes z .. zc + NS; p of plane zc
   T lr[CPT], lp[CPT], lq[CPT], Bc[CPT], acc[CPT], ev[CC];
+  // FP64: the sums leave no registers for several columns' accesses in flight;
+  // columns without a point are branched around
+  constexpr bool BR = sizeof(T) == 8;
   PRestrict<CC, T> R;
   PSums s{0.0, 0.0, 0.0};
   const int z0 = -Zmax - 2 + (Zmax & 1);
   const int zl = pcg_last_step(M, Zmax) + NS;
+  PBase<NS + 2> pb(pst, Zmax, z0 - NS);   // planes zc - NS .. zc + 1
 #pragma unroll
   for (int u = 0; u < CC; ++u) R.acc2[u] = 0;
 #pragma unroll
@@ -546,82 +713,89 @@ __device__ __forceinline__ PSums pcg_sweep_tl(const GenStencilT<T>& G, const MgU
     lr[c] = lp[c] = lq[c] = Bc[c] = acc[c] = 0;
 #pragma unroll
     for (int k = 0; k < 2 * NS + 1; ++k) sum[c][k] = 0;
-#pragma unroll
-    for (int k = 0; k < NS + 1; ++k) pd[c][k] = 0;
   }
-  auto load_e = [&](int kz) {
-    const unsigned base = PBase<1>::at(cst, M.Z1, kz) + threadIdx.x;
+  auto load_e = [&](int kz) {   // a level-1 plane of the correction
+    const unsigned base = V.e1 + PBase<1>::at(cst, M.Z1, kz) * (unsigned)sizeof(T);
 #pragma unroll
     for (int u = 0; u < CC; ++u) {
-      ev[u] = 0;
-      if (kz >= ck.lo[u] && kz <= ck.hi[u]) ev[u] = gload(e1, base + u * NT);
+      const PHalves iv(ck.iv[u]);
+      ev[u] = bload<T>(V.all, kz >= iv.a && kz <= iv.b ? (threadIdx.x + u * NT) * (unsigned)sizeof(T) : kOob, base);
     }
   };
   load_e((z0 + 2) >> 1);
-  PBase<NS + 2> pb(pst, Zmax, z0 - NS);   // planes zc - NS .. zc + 1
-  for (int zc = z0; zc <= zl; ++zc) {
+  auto body = [&](auto odd, int zc) __attribute__((always_inline)) {
+    constexpr bool ODD = decltype(odd)::value, ZODD = ODD != (bool)(NS & 1);
     const int z = zc - NS;
+    // byte offsets of planes zc - NS .. of a vector: V.x + at(k)
+    auto at = [&](int k) __attribute__((always_inline)) { return pb.b[k] * (unsigned)sizeof(T); };
+    if constexpr (ODD) load_e((zc + 3) >> 1);
+    const GenStencilT<T> G = gen_args<T>(a);
     T* pl = L.pl0 + ((zc & 1) ? L.plane : 0);
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
       T pe = Bc[c];
-      if (zc & 1) {
-        const T Bn = EXX_PHAS(c) ? prolong4<T>(L.E, cl.xy[c], M) : (T)0;
+      if constexpr (ODD) {
+        const T Bn = prolong4<T>(L.E, cl.re[c], M);
         pe = (T)0.5 * (pe + Bn);
         Bc[c] = Bn;
       }
-#pragma unroll
-      for (int k = 0; k < NS; ++k) pd[c][k] = pd[c][k + 1];
+      const PCol<GEN> k = cl.get(c);
+      const bool in = k.valid(zc);
+      const unsigned vo = pcg_off<T>(k, in);
       T v = 0;
-      if (EXX_PVALID(c, zc)) {
-        const unsigned idx = EXX_PIDX(c, pb.b[NS]);
-        T rn = lr[c];
-        if (!first) {
-          rn -= alpha * lq[c];
-          gstore(r, idx, rn);
-        }
-        v = w0 * rn + pe;
-        if (!first) v += beta * lp[c];
-        gstore(pn, idx, v);
+      if (!BR || in) {
+        const T rn = lr[c] - alpha * lq[c];
+        v = (w0 * rn + pe) + beta * lp[c];
+        v = in ? v : (T)0;
+        bstore<T>(V.all, vo, V.r + at(NS), rn);
+        bstore<T>(V.all, vo, V.pn + at(NS), v);
         s.rr += (double)rn * (double)rn;
       }
-      pd[c][NS] = v;
-      if (EXX_PHAS(c)) pl[EXX_PPOS(c)] = v;
-      lr[c] = lp[c] = lq[c] = 0;
-      if (EXX_PVALID(c, zc + 1)) {
-        const unsigned idx = EXX_PIDX(c, pb.b[NS + 1]);
-        lr[c] = gload(r, idx);
-        if (!first) {
-          lp[c] = gload(p, idx);
-          lq[c] = gload(q, idx);
-        }
-      }
+      pv[c] = v;
+      pl[k.low + NS * kLdsWX] = v;
     }
-    if (!(zc & 1)) {   // level-1 plane (zc + 2) / 2, interpolated in the next step
-#pragma unroll
-      for (int u = 0; u < CC; ++u)
-        if (ck.lo[u] <= ck.hi[u]) L.E[fresh(ck.ep[u])] = ev[u];
-    }
-    __syncthreads();
-    if (zc & 1) load_e((zc + 3) >> 1);
-    if (z >= -Zmax) pcg_restrict_step<CC, NT, T>(M, ck, L, cst, z, R, g1, g2);
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
-      if (EXX_PHAS(c) && zc <= Zmax + NS)
-        tl_scatter<NS, T>(G, pd[c][NS], EXX_PVALID(c, zc), pl, EXX_PPOS(c), sum[c]);
-      T qv = 0;
-      if (EXX_PVALID(c, z)) {
-        qv = -sum[c][0];
-        gstore(q, EXX_PIDX(c, pb.b[0]), qv);
-        s.pq += (double)pd[c][0] * (double)qv;
+      const PCol<GEN> k = cl.get(c);
+      const bool in = k.valid(zc + 1);
+      const unsigned vo = pcg_off<T>(k, in);
+      if constexpr (BR) lr[c] = lp[c] = lq[c] = 0;
+      if (!BR || in) {
+        lr[c] = bload<T>(V.all, vo, V.r + at(NS + 1));
+        lp[c] = bload<T>(V.all, vo | V.none, V.p + at(NS + 1));
+        lq[c] = bload<T>(V.all, vo | V.none, V.q + at(NS + 1));
+      }
+    }
+    if constexpr (!ODD) {   // level-1 plane (zc + 2) / 2, interpolated in the next step
+#pragma unroll
+      for (int u = 0; u < CC; ++u) {
+        const PHalves iv(ck.iv[u]);
+        if (iv.a <= iv.b) L.E[PHalves(ck.ps[u]).b] = ev[u];
+      }
+    }
+    __syncthreads();
+    if constexpr (ZODD)
+      pcg_restrict_odd<CC, T>(M, ck, L, z, V.all, V.g2);
+    else
+      pcg_restrict_even<CC, NT, T>(M, ck, L, cst, z, R, V.all, V.g1);
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) {
+      const PCol<GEN> k = cl.get(c);
+      const T below = sum[c][NS];
+      if (k.near(zc, NS)) pcg_scatter<NS, T>(G, pv[c], k.valid(zc), pl, k.low + NS * kLdsWX, sum[c]);
+      s.pq -= (double)pv[c] * ((double)below + (double)sum[c][NS]);
+      const bool in = k.valid(z);
+      const T qv = in ? -sum[c][0] : (T)0;
+      if (!BR || in) {
+        bstore<T>(V.all, pcg_off<T>(k, in), V.q + at(0), qv);
         s.qq += (double)qv * (double)qv;
       }
 #pragma unroll
       for (int k = 0; k < 2 * NS; ++k) sum[c][k] = sum[c][k + 1];
       sum[c][2 * NS] = 0;
-      if (z & 1) {
+      if constexpr (ZODD) {
         const T h = (T)0.5 * qv;
-        if (EXX_PHAS(c)) L.R1[EXX_PR1(c)] = acc[c] + h;
+        L.R1[EXX_PR1(c)] = acc[c] + h;
         acc[c] = h;
       } else {
         acc[c] += qv;
@@ -629,6 +803,10 @@ __device__ __forceinline__ PSums pcg_sweep_tl(const GenStencilT<T>& G, const MgU
     }
     pb.next(pst, Zmax, zc - NS);
     if (L.plane == 0) __syncthreads();   // one plane: its readers are done
+  };
+  for (int zc = z0; zc <= zl; zc += 2) {
+    body(std::false_type(), zc);
+    body(std::true_type(), zc + 1);
   }
   __syncthreads();
   return s;
@@ -636,9 +814,10 @@ __device__ __forceinline__ PSums pcg_sweep_tl(const GenStencilT<T>& G, const MgU
 
 // The restriction of a residual that is not followed from the one before (the
 // first one): the streamed part of the sweep alone.
-template <int CPT, int NT, int CC, typename T, bool GEN>
-__device__ __forceinline__ void pcg_pass_r(const MgU& M, const PCols<CPT, GEN>& cl, const PCoarse<CC>& ck, const int* pst,
-                           const int* cst, int Zmax, const T* r, T* c1, T* b2, const PLds<T>& L) {
+template <int CPT, int NT, int CC, typename T, bool GEN, bool PK>
+__device__ __forceinline__ void pcg_pass_r(const MgU& M, const PCols<CPT, GEN, PK>& cl, const PCoarse<CC>& ck, const int* pst,
+                           const int* cst, int Zmax, const T* r, const PVec& V, unsigned c1, unsigned b2,
+                           const PLds<T>& L) {
   T cr[CPT], acc[CPT];
   PRestrict<CC, T> R;
   PBase<2> pb(pst, Zmax, -Zmax);
@@ -655,7 +834,7 @@ __device__ __forceinline__ void pcg_pass_r(const MgU& M, const PCols<CPT, GEN>& 
 #pragma unroll
     for (int c = 0; c < CPT; ++c) nr[c] = EXX_PVALID(c, z + 1) ? gload(r, EXX_PIDX(c, pb.b[1])) : (T)0;
     __syncthreads();
-    pcg_restrict_step<CC, NT, T>(M, ck, L, cst, z, R, c1, b2);
+    pcg_restrict_step<CC, NT, T>(M, ck, L, cst, z, R, V.all, c1, b2);
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
       if (z & 1) {
@@ -677,11 +856,11 @@ __device__ __forceinline__ void pcg_pass_r(const MgU& M, const PCols<CPT, GEN>& 
 // restriction of that.  pl0 and pl0 + plane are FP64 planes; L holds the
 // working precision's buffers of the restriction.  Returns this thread's sum of
 // the true residual^2.
-template <int NS, int CPT, int NT, bool GEN, int CC, typename T>
-__device__ __forceinline__ double pcg_residual(const SolveKArgs& a, const MgU& M, const PCols<CPT, GEN>& cl, const PCoarse<CC>& ck,
+template <int NS, int CPT, int NT, bool GEN, int CC, typename T, bool PK>
+__device__ __forceinline__ double pcg_residual(const SolveKArgs& a, const MgU& M, const PCols<CPT, GEN, PK>& cl, const PCoarse<CC>& ck,
                                const int* pst, const int* cst, int Zmax, const double* __restrict__ x,
                                const double* __restrict__ b, T* __restrict__ r, double rs, double* pl0,
-                               int plane, T* c1, T* b2, const PLds<T>& L) {
+                               int plane, const PVec& V, unsigned c1, unsigned b2, const PLds<T>& L) {
   double win[CPT][2 * NS + 1];
   T acc[CPT];
   PRestrict<CC, T> R;
@@ -711,7 +890,7 @@ __device__ __forceinline__ double pcg_residual(const SolveKArgs& a, const MgU& M
     for (int c = 0; c < CPT; ++c)
       if (EXX_PHAS(c)) pl[EXX_PPOS(c)] = win[c][NS];
     __syncthreads();
-    pcg_restrict_step<CC, NT, T>(M, ck, L, cst, z, R, c1, b2);
+    pcg_restrict_step<CC, NT, T>(M, ck, L, cst, z, R, V.all, c1, b2);
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
       T rn = 0;
@@ -739,11 +918,11 @@ __device__ __forceinline__ double pcg_residual(const SolveKArgs& a, const MgU& M
   return sum;
 }
 
-template <int NS, int CPT, int NT, int CC, typename T, bool GEN = true>
-__device__ __forceinline__ double pcg_residual_tl(const SolveKArgs& a, const MgU& M, const PCols<CPT, GEN>& cl, const PCoarse<CC>& ck,
+template <int NS, int CPT, int NT, int CC, typename T, bool GEN = true, bool PK = false>
+__device__ __forceinline__ double pcg_residual_tl(const SolveKArgs& a, const MgU& M, const PCols<CPT, GEN, PK>& cl, const PCoarse<CC>& ck,
                                   const int* pst, const int* cst, int Zmax, const double* __restrict__ x,
                                   const double* __restrict__ b, T* __restrict__ r, double rs, double* pl0,
-                                  int plane, T* c1, T* b2, const PLds<T>& L) {
+                                  int plane, const PVec& V, unsigned c1, unsigned b2, const PLds<T>& L) {
   double acc[CPT][2 * NS + 1], cx[CPT];
   T ra[CPT];
   PRestrict<CC, T> R;
@@ -772,7 +951,7 @@ __device__ __forceinline__ double pcg_residual_tl(const SolveKArgs& a, const MgU
     for (int c = 0; c < CPT; ++c)
       if (EXX_PHAS(c)) pl[EXX_PPOS(c)] = cx[c];
     __syncthreads();
-    if (zo >= -Zmax) pcg_restrict_step<CC, NT, T>(M, ck, L, cst, zo, R, c1, b2);
+    pcg_restrict_step<CC, NT, T>(M, ck, L, cst, zo, R, V.all, c1, b2);
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
       if (EXX_PHAS(c) && z <= Zmax + NS)
@@ -911,23 +1090,20 @@ __device__ __forceinline__ void pcg_coarse(const MgDev& M, const double* wl, T* 
   __syncthreads();
 }
 
-template <int NS, int CPT, int NT, bool GEN, bool TL, bool RQ, int CC, typename T>
-__device__ __forceinline__ PSums pcg_sweep(const StencilT<T>& S, const GenStencilT<T>& G, const MgU& M,
-                                           const PCols<CPT, GEN>& cl, const PCoarse<CC>& ck, const int* pst,
-                                           const int* cst, int Zmax, T* r, T* q, const T* p, T* pn, const T* e1, T w0,
-                                           T alpha, T beta, bool first, T* g1, T* g2, const PLds<T>& L) {
+template <int NS, int CPT, int NT, bool GEN, bool TL, bool RQ, int CC, typename T, bool PK>
+__device__ __forceinline__ PSums pcg_sweep(const SolveKArgs& a, const StencilT<T>& S, const GenStencilT<T>& G, const MgU& M,
+                                           const PCols<CPT, GEN, PK>& cl, const PCoarse<CC>& ck, const int* pst,
+                                           const int* cst, int Zmax, const PVec& V, T w0, T alpha, T beta,
+                                           const PLds<T>& L) {
   w0 = uniform(w0);
   alpha = uniform(alpha);
   beta = uniform(beta);
   if constexpr (TL)
-    return pcg_sweep_tl<NS, CPT, NT, CC, T>(G, M, cl, ck, pst, cst, Zmax, r, q, p, pn, e1, w0, alpha, beta, first, g1,
-                                            g2, L);
+    return pcg_sweep_tl<NS, CPT, NT, CC, T>(a, M, cl, ck, pst, cst, Zmax, V, w0, alpha, beta, L);
   else if constexpr (RQ)
-    return pcg_sweep_rq<NS, CPT, NT, GEN, CC, T>(S, G, M, cl, ck, pst, cst, Zmax, r, p, pn, e1, w0, alpha, beta, first,
-                                                 g1, g2, L);
+    return pcg_sweep_rq<NS, CPT, NT, GEN, CC, T>(S, G, M, cl, ck, pst, cst, Zmax, V, w0, alpha, beta, L);
   else
-    return pcg_sweep_w<NS, CPT, NT, GEN, CC, T>(S, G, M, cl, ck, pst, cst, Zmax, r, q, p, pn, e1, w0, alpha, beta,
-                                                first, g1, g2, L);
+    return pcg_sweep_w<NS, CPT, NT, GEN, CC, T>(S, G, M, cl, ck, pst, cst, Zmax, V, w0, alpha, beta, L);
 }
 
 // The last directions and their steps, not yet added to x: buffers lo .. n - 1
@@ -1000,6 +1176,7 @@ struct PDir {
 template <typename T>
 struct PSlot {
   T *r, *q, *p0, *c1, *g1, *e1, *b2, *g2;
+  int bytes;
   __device__ __forceinline__ PSlot(T* base, const SolveKArgs& a) {
     r = base;
     q = r + a.sstride;
@@ -1009,6 +1186,22 @@ struct PSlot {
     e1 = g1 + a.c1stride;
     b2 = e1 + a.c1stride;
     g2 = b2 + a.b2stride;
+    bytes = uniform((int)((char*)(g2 + a.b2stride) - (char*)base));
+  }
+  __device__ __forceinline__ unsigned off(const T* v) const { return (unsigned)uniform((int)((char*)v - (char*)r)); }
+  // the vectors of a sweep from the direction in buffer `from` of the ring to `to`
+  __device__ __forceinline__ PVec vec(const SolveKArgs& a, int from, int to, bool first) const {
+    PVec V;
+    V.all = pbuf(r, bytes);
+    V.none = first ? kOob : 0u;
+    V.r = 0;
+    V.q = off(q);
+    V.p = off(p0 + from * a.sstride);
+    V.pn = off(p0 + to * a.sstride);
+    V.e1 = off(e1);
+    V.g1 = off(g1);
+    V.g2 = off(g2);
+    return V;
   }
 };
 
@@ -1035,7 +1228,7 @@ __global__ __launch_bounds__(NT) void k_pcg(SolveKArgs a) {
     const long long item = row - a.p0;
     const int pid = uniform(a.order[row]);
     const ClassDev& C = a.cls[uniform(a.pairs[pid].cls)];
-    const MgU M = mg_uniform(C.mg, a.lds_cx, a.lds_cy);
+    const MgU M = mg_uniform(C.mg);
     const int Zmax = uniform(C.Zmax);
     const int npe = uniform((int)C.n_pe);
     double* x = a.bx_ws + item * a.rstride;
@@ -1051,8 +1244,8 @@ __global__ __launch_bounds__(NT) void k_pcg(SolveKArgs a) {
     EXX_PFOR(k, 2 * Zmax + 2) pst[k] = C.plane_start[k];
     EXX_PFOR(k, 2 * M.Z1 + 2) cst[k] = C.mg.c1start[k];
     EXX_PFOR(k, M.d2xy * C.mg.D2[2]) W.b2[k] = W.g2[k] = 0.0;
-    PCols<CPT, GEN> cl;
-    pcg_cols<CPT, NT, GEN>(C, a.lds_cx, a.lds_cy, cl);
+    PCols<CPT, GEN, true> cl;
+    pcg_cols<NS, CPT, NT, GEN>(C, a.lds_cx, a.lds_cy, cl);
     PCoarse<CC> ck;
     pcg_coarse_cols<CC, NT>(C, ck);
     const bool padded = uniform((int)C.n_real) != npe;
@@ -1080,10 +1273,10 @@ __global__ __launch_bounds__(NT) void k_pcg(SolveKArgs a) {
         double t;
         if constexpr (TL)
           t = pcg_residual_tl<NS, CPT, NT, CC, double>(a, M, cl, ck, pst, cst, Zmax, W.p0, x, W.r, 1.0, lds, L.plane,
-                                                       W.c1, W.b2, L);
+                                                       W.vec(a, 0, 0, true), W.off(W.c1), W.off(W.b2), L);
         else
           t = pcg_residual<NS, CPT, NT, GEN, CC, double>(a, M, cl, ck, pst, cst, Zmax, W.p0, x, W.r, 1.0, lds, L.plane,
-                                                         W.c1, W.b2, L);
+                                                         W.vec(a, 0, 0, true), W.off(W.c1), W.off(W.b2), L);
         rr = uniform(block_sum(t, red));
         EXX_PFOR(k, npe) x[k] = W.p0[k];
         x_zero = false;
@@ -1093,7 +1286,7 @@ __global__ __launch_bounds__(NT) void k_pcg(SolveKArgs a) {
       } else {
         EXX_PFOR(k, npe) W.r[k] = x[k];
         __syncthreads();
-        pcg_pass_r<CPT, NT, CC, double, GEN>(M, cl, ck, pst, cst, Zmax, W.r, W.c1, W.b2, L);
+        pcg_pass_r<CPT, NT, CC, double, GEN>(M, cl, ck, pst, cst, Zmax, W.r, W.vec(a, 0, 0, true), W.off(W.c1), W.off(W.b2), L);
       }
     }
     PRing ring;
@@ -1115,10 +1308,9 @@ __global__ __launch_bounds__(NT) void k_pcg(SolveKArgs a) {
         x_zero = false;
         ring.lo = ring.n = 0;
       }
-      double* pn = W.p0 + ring.n * a.sstride;
-      const double* p = W.p0 + (ring.n + kPcgRing - 1) % kPcgRing * a.sstride;
-      const PSums s = pcg_sweep<NS, CPT, NT, GEN, TL, false, CC, double>(a.S, a.G, M, cl, ck, pst, cst, Zmax, W.r, W.q, p, pn,
-                                                                  W.e1, a.wl[0], alpha, dir.beta, first, W.g1, W.g2, L);
+      const PVec V = W.vec(a, (ring.n + kPcgRing - 1) % kPcgRing, ring.n, first);
+      const PSums s = pcg_sweep<NS, CPT, NT, GEN, TL, false, CC, double>(a, a.S, a.G, M, cl, ck, pst, cst, Zmax, V,
+                                                                         a.wl[0], alpha, dir.beta, L);
       double v[4] = {s.rr, s.pq, s.qq, 0.0};
       block_sum4(v, red);
       const double rrn = uniform(v[0]);
@@ -1197,7 +1389,7 @@ __global__ __launch_bounds__(NT) void k_pcg_mixed(SolveKArgs a) {
     const long long item = row - a.p0;
     const int pid = uniform(a.order[row]);
     const ClassDev& C = a.cls[uniform(a.pairs[pid].cls)];
-    const MgU M = mg_uniform(C.mg, a.lds_cx, a.lds_cy);
+    const MgU M = mg_uniform(C.mg);
     const int Zmax = uniform(C.Zmax);
     const int npe = uniform((int)C.n_pe);
     double* bx = a.bx_ws + item * a.rstride;
@@ -1213,8 +1405,8 @@ __global__ __launch_bounds__(NT) void k_pcg_mixed(SolveKArgs a) {
     EXX_PFOR(k, 2 * Zmax + 2) pst[k] = C.plane_start[k];
     EXX_PFOR(k, 2 * M.Z1 + 2) cst[k] = C.mg.c1start[k];
     EXX_PFOR(k, M.d2xy * C.mg.D2[2]) W.b2[k] = W.g2[k] = 0.0f;
-    PCols<CPT, GEN> cl;
-    pcg_cols<CPT, NT, GEN>(C, a.lds_cx, a.lds_cy, cl);
+    PCols<CPT, GEN, false> cl;
+    pcg_cols<NS, CPT, NT, GEN>(C, a.lds_cx, a.lds_cy, cl);
     PCoarse<CC> ck;
     pcg_coarse_cols<CC, NT>(C, ck);
     const bool padded = uniform((int)C.n_real) != npe;
@@ -1257,17 +1449,17 @@ __global__ __launch_bounds__(NT) void k_pcg_mixed(SolveKArgs a) {
           EXX_PFOR(k, npe) W.r[k] = (float)(bx[k] * inv_b);
         __syncthreads();
         if (need == 1) {
-          pcg_pass_r<CPT, NT, CC, float, GEN>(M, cl, ck, pst, cst, Zmax, W.r, W.c1, W.b2, L);
+          pcg_pass_r<CPT, NT, CC, float, GEN>(M, cl, ck, pst, cst, Zmax, W.r, W.vec(a, 0, 0, true), W.off(W.c1), W.off(W.b2), L);
           rr_true = bb;
         } else {
           double t;
           const int pl2 = a.pcg_planes == 2 ? plane : 0;
           if constexpr (TL)
             t = pcg_residual_tl<NS, CPT, NT, CC, float>(a, M, cl, ck, pst, cst, Zmax, x, bx, W.r, inv_b, lds, pl2,
-                                                        W.c1, W.b2, L);
+                                                        W.vec(a, 0, 0, true), W.off(W.c1), W.off(W.b2), L);
           else
             t = pcg_residual<NS, CPT, NT, GEN, CC, float>(a, M, cl, ck, pst, cst, Zmax, x, bx, W.r, inv_b, lds, pl2,
-                                                          W.c1, W.b2, L);
+                                                          W.vec(a, 0, 0, true), W.off(W.c1), W.off(W.b2), L);
           rr_true = uniform(block_sum(t, red));
         }
         EXX_PFOR(k, a.pcg_lds) fl[k] = 0.0f;
@@ -1294,11 +1486,9 @@ __global__ __launch_bounds__(NT) void k_pcg_mixed(SolveKArgs a) {
         y_zero = false;
         ring.lo = ring.n = 0;
       }
-      float* pn = W.p0 + ring.n * a.sstride;
-      const float* p = W.p0 + (ring.n + kPcgRing - 1) % kPcgRing * a.sstride;
-      const PSums s = pcg_sweep<NS, CPT, NT, GEN, TL, RQ, CC, float>(S32, a.G32, M, cl, ck, pst, cst, Zmax, W.r, W.q, p, pn,
-                                                                 W.e1, (float)a.wl[0], (float)alpha, (float)dir.beta,
-                                                                 first, W.g1, W.g2, L);
+      const PVec V = W.vec(a, (ring.n + kPcgRing - 1) % kPcgRing, ring.n, first);
+      const PSums s = pcg_sweep<NS, CPT, NT, GEN, TL, RQ, CC, float>(a, S32, a.G32, M, cl, ck, pst, cst, Zmax, V,
+                                                                     (float)a.wl[0], (float)alpha, (float)dir.beta, L);
       double v[4] = {s.rr, s.pq, s.qq, 0.0};
       block_sum4(v, red);
       const double rrn = uniform(v[0]);

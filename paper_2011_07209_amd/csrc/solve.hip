@@ -70,8 +70,13 @@ long long pcg_slot_bytes(bool mixed, long long sstride, long long c1stride, long
   return (b + 255) & ~255LL;
 }
 
+// (the columns of each level one or two to a thread, and what the kernels pack
+// into 16, 14, 13, 12 and 6 bits: see PCols and PCoarse)
 bool pcg_supported(const Geo& g, const ClassHost& C, bool mixed) {
-  return C.mg.n_c1 > 0 && C.mg.n_c1 <= 1024 && C.mg.n_c2 <= 512 && (int)C.fin_cols.size() <= 4096 &&
+  const MgDev& M = C.mg;
+  return M.n_c1 > 0 && M.n_c1 <= 1024 && M.n_c2 <= 512 && C.n_cols <= 4096 && (int)C.fin_cols.size() <= 4096 &&
+         (long long)kLdsWX * g.lds_wy <= 8192 && C.Zmax < 126 && (long long)M.rw * M.rh <= 32768 &&
+         (long long)M.ew * M.eh <= 16384 && (long long)M.D2[0] * M.D2[1] <= 32768 &&
          pcg_planes(g, C.mg, C.Zmax, mixed) > 0;
 }
 
