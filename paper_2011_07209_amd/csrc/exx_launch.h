@@ -66,7 +66,8 @@ struct SolveArgs {
   const int* order = nullptr;
   long long p0 = 0, npair = 0;   // batch start and capacity
   const int* n_eff = nullptr;    // device pair count of the processing order
-  int cls_id = -1;               // >= 0: solve only this class's rows of the batch
+  int cls_id = -1;               // >= 0: solve only the rows of classes cls_lo .. cls_id of the batch
+  int cls_lo = -1;
   const int* class_cnt = nullptr;   // device per-class pair counts of the order
   int ncls = 1;
   int* queue = nullptr;
@@ -82,7 +83,8 @@ struct SolveArgs {
   double tol = 0;
   int max_iter = 0;
   bool mixed = false;
-  double delta = 0.01;         // mixed: reliable-update threshold
+  double delta = 0.01;         // mixed: reliable-update threshold,
+  double cls_delta[kMaxClasses] = {};   // preconditioned CG: or the class's own (> 0)
   // warm start (warm_store null: every solve starts from zero)
   const float* warm_store = nullptr;   // [2][warm_cap][rstride] FP32 solutions
   long long warm_cap = 0;
@@ -111,6 +113,18 @@ long long solve_slot_bytes(bool mixed, long long sstride);
 // per CU (0: this variant cannot run it) and its slot size.
 bool pcg_supported(const Geo& g, const ClassHost& C, bool mixed);
 int pcg_groups_per_cu(const Geo& g, const ClassHost& C, bool mixed, int threads);
+// Columns per thread of the preconditioned CG's kernel instance: up to 4 with
+// 1024 and 768 threads, up to 8 with 512.
+inline int pcg_cpt(int cols, int threads) {
+  const int c = (cols + threads - 1) / threads;
+  if (threads == 768) return (c + 1) / 2 * 2;
+  if (threads == 512) return c <= 4 ? 4 : (c + 1) / 2 * 2;
+  return c;
+}
+// The dims that hold the nested grids of both.
+MgDev pcg_join(const MgDev& a, const MgDev& b);
+// Whether the joined class still runs with as many planes in LDS.
+bool pcg_joins(const Geo& g, const MgDev& joined, const MgDev& one, int zmax, bool mixed);
 long long pcg_slot_bytes(bool mixed, long long sstride, long long c1stride, long long b2stride);
 hipError_t launch_finalize(const Geo& g, const Batch& B, const double* rho_ws, const double* v_ws, long long rstride,
                            const double* halo_ws, long long hstride, double* outE, double* outS, hipStream_t s);

@@ -1388,7 +1388,9 @@ __global__ __launch_bounds__(NT) void k_pcg_mixed(SolveKArgs a) {
     if (row >= hi) break;
     const long long item = row - a.p0;
     const int pid = uniform(a.order[row]);
-    const ClassDev& C = a.cls[uniform(a.pairs[pid].cls)];
+    const int cls = uniform(a.pairs[pid].cls);
+    const ClassDev& C = a.cls[cls];
+    const double delta = a.cls_delta[cls];
     const MgU M = mg_uniform(C.mg);
     const int Zmax = uniform(C.Zmax);
     const int npe = uniform((int)C.n_pe);
@@ -1518,7 +1520,7 @@ __global__ __launch_bounds__(NT) void k_pcg_mixed(SolveKArgs a) {
         need = x_zero ? 1 : 2;
         continue;
       }
-      if (!first && (rnorm < a.delta * rmax || rnorm <= a.tol || it >= a.max_iter)) {
+      if (!first && (rnorm < delta * rmax || rnorm <= a.tol || it >= a.max_iter)) {
         // reliable update: the FP32 correction folded into the FP64 solution,
         // x = x + ||b|| y, with the deferred step
         pcg_flush<NT, double, float>(x, x_zero, bnorm, y_zero ? nullptr : y, ring, W.p0, a.sstride, npe);
@@ -1578,30 +1580,20 @@ hipError_t pcg_instance(const SolveKArgs& a, int groups, size_t lds, hipStream_t
   return pcg_instance_g<NS, CPT, NT, true, false, MIXED>(a, groups, lds, s, occ);
 }
 
-// Columns per thread: up to 4 with 1024 and 768 threads, up to 8 with 512.
 template <int NS, bool MIXED>
 hipError_t pcg_dispatch(const SolveKArgs& a, int cols, int threads, int groups, size_t lds, hipStream_t s, int* occ) {
-  const int cpt = (cols + threads - 1) / threads;
-  if (threads == 1024) {
-    switch (cpt) {
-      case 1: return pcg_instance<NS, 1, 1024, MIXED>(a, groups, lds, s, occ);
-      case 2: return pcg_instance<NS, 2, 1024, MIXED>(a, groups, lds, s, occ);
-      case 3: return pcg_instance<NS, 3, 1024, MIXED>(a, groups, lds, s, occ);
-      case 4: return pcg_instance<NS, 4, 1024, MIXED>(a, groups, lds, s, occ);
-      default: return hipErrorInvalidValue;
-    }
+  switch (16 * threads + pcg_cpt(cols, threads)) {
+    case 16 * 1024 + 1: return pcg_instance<NS, 1, 1024, MIXED>(a, groups, lds, s, occ);
+    case 16 * 1024 + 2: return pcg_instance<NS, 2, 1024, MIXED>(a, groups, lds, s, occ);
+    case 16 * 1024 + 3: return pcg_instance<NS, 3, 1024, MIXED>(a, groups, lds, s, occ);
+    case 16 * 1024 + 4: return pcg_instance<NS, 4, 1024, MIXED>(a, groups, lds, s, occ);
+    case 16 * 768 + 2: return pcg_instance<NS, 2, 768, MIXED>(a, groups, lds, s, occ);
+    case 16 * 768 + 4: return pcg_instance<NS, 4, 768, MIXED>(a, groups, lds, s, occ);
+    case 16 * 512 + 4: return pcg_instance<NS, 4, 512, MIXED>(a, groups, lds, s, occ);
+    case 16 * 512 + 6: return pcg_instance<NS, 6, 512, MIXED>(a, groups, lds, s, occ);
+    case 16 * 512 + 8: return pcg_instance<NS, 8, 512, MIXED>(a, groups, lds, s, occ);
+    default: return hipErrorInvalidValue;
   }
-  if (threads == 768) {
-    if (cpt <= 2) return pcg_instance<NS, 2, 768, MIXED>(a, groups, lds, s, occ);
-    if (cpt <= 4) return pcg_instance<NS, 4, 768, MIXED>(a, groups, lds, s, occ);
-    return hipErrorInvalidValue;
-  }
-  if (threads == 512) {
-    if (cpt <= 4) return pcg_instance<NS, 4, 512, MIXED>(a, groups, lds, s, occ);
-    if (cpt <= 6) return pcg_instance<NS, 6, 512, MIXED>(a, groups, lds, s, occ);
-    if (cpt <= 8) return pcg_instance<NS, 8, 512, MIXED>(a, groups, lds, s, occ);
-  }
-  return hipErrorInvalidValue;
 }
 
 }  // namespace exx

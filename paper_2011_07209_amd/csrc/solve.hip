@@ -63,6 +63,26 @@ static int pcg_planes(const Geo& g, const MgDev& M, int zmax, bool mixed) {
   return 0;
 }
 
+MgDev pcg_join(const MgDev& a, const MgDev& b) {
+  MgDev m = a;
+  m.Z1 = std::max(a.Z1, b.Z1);
+  m.rw = std::max(a.rw, b.rw);
+  m.rh = std::max(a.rh, b.rh);
+  m.ew = std::max(a.ew, b.ew);
+  m.eh = std::max(a.eh, b.eh);
+  for (int k = 0; k < 3; ++k) {
+    m.D2[k] = std::max(a.D2[k], b.D2[k]);
+    m.D3[k] = std::max(a.D3[k], b.D3[k]);
+    m.D4[k] = std::max(a.D4[k], b.D4[k]);
+  }
+  return m;
+}
+
+bool pcg_joins(const Geo& g, const MgDev& joined, const MgDev& one, int zmax, bool mixed) {
+  const int planes = pcg_planes(g, joined, zmax, mixed);
+  return planes > 0 && planes == pcg_planes(g, one, zmax, mixed);
+}
+
 long long pcg_slot_bytes(bool mixed, long long sstride, long long c1stride, long long b2stride) {
   // r, q and the ring of p; the mixed solve's x (FP64) and y
   const long long b = (mixed ? 12 * sstride : 0) +
@@ -97,6 +117,7 @@ static hipError_t solve_dispatch(const SolveArgs& in, int max_cols, int max_zmax
   a.n = in.g.n;
   for (int ax = 0; ax < 3; ++ax) a.N[ax] = in.g.N[ax];
   a.cls_id = in.cls_id;
+  a.cls_lo = in.cls_lo >= 0 ? in.cls_lo : in.cls_id;
   a.class_cnt = in.class_cnt;
   a.ncls = in.ncls;
   a.queue = in.queue;
@@ -193,6 +214,7 @@ static hipError_t solve_dispatch(const SolveArgs& in, int max_cols, int max_zmax
   if (in.pcg_cols > 0) {
     a.slot_bytes = pcg_slot_bytes(in.mixed, in.sstride, in.c1stride, in.b2stride);
     a.c1stride = in.c1stride;
+    for (int k = 0; k < kMaxClasses; ++k) a.cls_delta[k] = in.cls_delta[k] > 0.0 ? in.cls_delta[k] : in.delta;
     a.b2stride = in.b2stride;
     a.pcg_planes = pcg_planes(in.g, in.mg, max_zmax, in.mixed);
     if (a.pcg_planes == 0) return hipErrorInvalidValue;

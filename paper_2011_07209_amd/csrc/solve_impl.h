@@ -121,7 +121,7 @@ struct SolveKArgs {
   const int* order;
   long long p0, npair;    // batch start and capacity; the batch holds min(npair, *n_eff - p0) pairs
   const int* n_eff;       // device pair count of the processing order
-  int cls_id;             // >= 0: only the rows of this sphere class (class_cnt, ncls give the ranges)
+  int cls_id, cls_lo;     // >= 0: only the rows of sphere classes cls_lo .. cls_id (class_cnt, ncls give the ranges)
   const int* class_cnt;
   int ncls;
   int* queue;
@@ -138,7 +138,8 @@ struct SolveKArgs {
   int* outExit;           // per pair: exit reason (kCg*) | restarts << 8
   double tol;
   int max_iter;
-  double delta;           // mixed: update when ||r|| < delta * (residual at the last update)
+  double delta;           // mixed: update when ||r|| < delta * (residual at the last update);
+  double cls_delta[kMaxClasses];   // preconditioned CG: by sphere class
   StencilT<double> S;
   int gen;                 // general cell: padded columns and the NK arms in G
   int quads;               // orthorhombic cell in the quad layout (one run of four columns per thread)
@@ -261,7 +262,8 @@ __device__ __forceinline__ void solve_range(const SolveKArgs& a, long long* lo, 
   if (a.cls_id >= 0) {
     long long start = 0;
     for (int k = a.ncls - 1; k > a.cls_id; --k) start += a.class_cnt[k];
-    const long long end = start + a.class_cnt[a.cls_id];
+    long long end = start;
+    for (int k = a.cls_id; k >= a.cls_lo; --k) end += a.class_cnt[k];
     if (l < start) l = start;
     if (h > end) h = end;
   }
