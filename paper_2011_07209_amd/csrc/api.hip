@@ -597,32 +597,16 @@ double cell_strain(const double h[9], const double h0[9]) {
   return m;
 }
 
-// Moment and boundary tables of every class for the plan's current offset
-// map, into the class block (same sizes as at assembly).
-exx_status upload_moment_tables(exx_plan_t P, const Geo& g) {
+// Moment and boundary tables of every class for the offset map of g, into the
+// class block (same sizes as at assembly); in place for every stream when it
+// returns.
+exx_status rewrite_moment_tables(exx_plan_t P, const Geo& g) {
   const bool mixed = P->opt.precision == EXX_PREC_MIXED;
   int mom_rows = 0, mom_mfma_rows = 0;
   moment_layout(P->l_max, mixed, &mom_rows, &mom_mfma_rows);
-  for (size_t k = 0; k < P->classes.size(); ++k) {
-    std::vector<double> btab;
-    build_boundary_table(P->classes[k], g.A, g.ylm_norm, P->l_max, &btab);
-    EXX_HIP(P, hipMemcpy((void*)P->class_dev_host[k].bnd_tab, btab.data(), btab.size() * sizeof(double),
-                         hipMemcpyHostToDevice));
-    std::vector<double> tab;
-    build_moment_table(P->classes[k], g.A, P->l_max, mom_rows, mixed ? 8 : 4, &tab);
-    const ClassDev& D = P->class_dev_host[k];
-    if (mixed) {
-      std::vector<unsigned short> hi(tab.size()), lo(tab.size());
-      for (size_t e = 0; e < tab.size(); ++e) {
-        hi[e] = bf16_rne((float)tab[e]);
-        lo[e] = bf16_rne((float)(tab[e] - bf16_value(hi[e])));
-      }
-      EXX_HIP(P, hipMemcpy((void*)D.mom_hi, hi.data(), hi.size() * sizeof(unsigned short), hipMemcpyHostToDevice));
-      EXX_HIP(P, hipMemcpy((void*)D.mom_lo, lo.data(), lo.size() * sizeof(unsigned short), hipMemcpyHostToDevice));
-    } else {
-      EXX_HIP(P, hipMemcpy((void*)D.mom_f64, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice));
-    }
-  }
+  for (size_t k = 0; k < P->classes.size(); ++k)
+    EXX_HIP(P, launch_cell_tables(g, P->class_dev_host[k], mixed, mom_rows, P->stream));
+  EXX_HIP(P, hipStreamSynchronize(P->stream));
   return EXX_OK;
 }
 
@@ -1026,7 +1010,7 @@ exx_status update_cell(exx_plan_t P, const double h[9]) {
       }
     }
   }
-  exx_status st = upload_moment_tables(P, g);
+  exx_status st = rewrite_moment_tables(P, g);
   if (st != EXX_OK) return st;
   P->geo = g;
   std::memcpy(P->h, h, sizeof(P->h));
