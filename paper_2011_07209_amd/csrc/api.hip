@@ -957,15 +957,16 @@ void default_solve_variants(exx_plan_t P) {
     // sphere's diameter): such a cap asks for that many plain CG steps.
     // Untuned, quad classes of mixed plans take the sweep without a stored q (768
     // threads, or 512), other classes 1024 threads up to 3 columns each; FP64
-    // without tilted arms up to 2, since three columns' windows spill to scratch
-    // memory there (2,957 columns, 2,356 pairs: 178 ms against 152 ms with 512).
+    // in orthorhombic cells up to 2, since three columns' windows spill to scratch
+    // memory there (2,957 columns, 2,356 pairs: 178 ms against 152 ms with 512;
+    // hexagonal, where the sweep branches: 64 ms against 84 ms, 533 pairs).
     P->class_pcg[k] = opt.solve_depth == 0 && opt.cg_max_iter >= 8 * (2 * P->classes[k].Zmax + 1) &&
                       pcg_supported(P->geo, P->classes[k], opt.precision == EXX_PREC_MIXED);
     if (P->class_pcg[k]) {
       const int cols = (int)P->classes[k].fin_cols.size();
       P->class_threads[k] = t ? t
                             : P->classes[k].quads && opt.precision == EXX_PREC_MIXED ? (nc <= 4 * 768 ? 768 : 512)
-                            : cols <= ((opt.precision == EXX_PREC_FP64 && !tilted_arms(P->geo)) ? 2 : 3) * 1024 ? 1024
+                            : cols <= ((opt.precision == EXX_PREC_FP64 && !P->geo.gen) ? 2 : 3) * 1024 ? 1024
                                                                                                                    : 512;
       P->class_depth[k] = 1;
       continue;
