@@ -127,6 +127,24 @@ struct CaptureGuard {
   ~CaptureGuard() { P->capturing = false; }
 };
 
+// Marks the plan as evaluating from the scratch array (its batch rows and CG
+// slots, and whether it runs the plain CG) for the lifetime of one exx_eval.
+struct ScratchGuard {
+  exx_plan_t P;
+  ScratchGuard(exx_plan_t p, long long rows, int slots, bool plain) : P(p) {
+    P->no_alloc = true;
+    P->batch_limit = rows;
+    P->slot_limit = slots;
+    P->plain_call = plain;
+  }
+  ~ScratchGuard() {
+    P->no_alloc = false;
+    P->batch_limit = 0;
+    P->slot_limit = 0;
+    P->plain_call = false;
+  }
+};
+
 // The plan's active workspace pointers as one EvalWork, and back.
 EvalWork get_work(exx_plan_t P) {
   EvalWork w;
@@ -292,11 +310,12 @@ int class_groups_per_cu(exx_plan_t P, int k, int threads, int depth) {
   return solve_groups_per_cu(P->geo, C.n_cols, C.Zmax, mixed, C.quads, threads, depth);
 }
 
-// Bytes of a workgroup's slot: the largest that a class's solver needs.
-long long plan_slot_bytes(exx_plan_t P) {
+// Bytes of a workgroup's slot: the largest that a class's solver needs (plain:
+// with the plain CG for every class).
+long long plan_slot_bytes(exx_plan_t P, bool plain) {
   const bool mixed = P->opt.precision == EXX_PREC_MIXED;
   long long b = solve_slot_bytes(mixed, slot_stride(P));
-  if (!P->pcg_off)
+  if (!plain)
     for (char on : P->class_pcg)
       if (on) return std::max(b, pcg_slot_bytes(mixed, slot_stride(P), P->max_c1, P->max_b2));
   return b;
@@ -307,7 +326,7 @@ void class_solve_args(exx_plan_t P, int k, SolveArgs* a) {
   const ClassHost& C = P->classes[k];
   a->quads = C.quads;
   a->pcg_cols = 0;
-  if (P->class_pcg[k] && !P->pcg_off) {
+  if (P->class_pcg[k] && !P->plain_call) {
     a->pcg_cols = (int)C.fin_cols.size();
     a->mg = C.mg;
     a->c1stride = P->max_c1;
@@ -351,7 +370,7 @@ exx_status select_solve(exx_plan_t P, int threads, int depth, int cls) {
 exx_status ensure_slots(exx_plan_t P) {
   if (P->slot_ws) return EXX_OK;
   char* sw = nullptr;
-  const long long sb = plan_slot_bytes(P);
+  const long long sb = plan_slot_bytes(P, false);
   if (dev_alloc(P, &sw, (size_t)P->n_slots * sb, "CG vectors")) return EXX_ENOMEM;
   P->slot_ws = sw;
   return EXX_OK;
@@ -1057,9 +1076,9 @@ void scratch_lookup(int dev) {
 }
 
 // Pieces of the scratch array (from base; base null: sizes only) for n_orb
-// orbitals, the plan's pair capacity, k batch rows and g CG slots.  Returns
-// the bytes the layout spans.
-size_t scratch_carve(exx_plan_t P, char* base, int n_orb, long long k, int g, EvalWork* w) {
+// orbitals, the plan's pair capacity, k batch rows and g CG slots (plain: of
+// the plain CG).  Returns the bytes the layout spans.
+size_t scratch_carve(exx_plan_t P, char* base, int n_orb, long long k, int g, bool plain, EvalWork* w) {
   size_t off = 0;
   auto take = [&](size_t bytes) -> char* {
     off = (off + 255) & ~(size_t)255;
@@ -1095,8 +1114,7 @@ size_t scratch_carve(exx_plan_t P, char* base, int n_orb, long long k, int g, Ev
                                    tail ? moment_splits(tail, ncls, P->max_pe) * tail : 0);
   w->Qp_ws = (double*)take(sizeof(double) * (size_t)(w->qp_rows * kMaxLM));
   w->n_slots = g;
-  w->slot_ws =
-      take((size_t)g * (size_t)plan_slot_bytes(P));
+  w->slot_ws = take((size_t)g * (size_t)plan_slot_bytes(P, plain));
   return off;
 }
 
@@ -1553,38 +1571,31 @@ exx_status exx_eval_noalloc(exx_plan_t P, int n_orb, const void* orbitals, exx_d
   const long long span = P->opt.max_pairs;
   long long lo = 1, hi = std::max<long long>(1, eval_batch(P, span));
   EvalWork w;
-  auto bytes_for = [&](long long k) {
-    return scratch_carve(P, nullptr, n_orb, k, (int)std::min<long long>(k, max_groups), &w);
-  };
   // (the preconditioned CG's slots are larger: where one does not fit, this call runs the plain CG)
-  P->pcg_off = bytes_for(1) > kScratchBytes;
-  if (bytes_for(1) > kScratchBytes) {
+  bool plain = false;
+  auto bytes_for = [&](long long k) {
+    return scratch_carve(P, nullptr, n_orb, k, (int)std::min<long long>(k, max_groups), plain, &w);
+  };
+  plain = bytes_for(1) > kScratchBytes;
+  if (bytes_for(1) > kScratchBytes)
     return fail(P, EXX_EINVAL, "exx_eval_noalloc: one pair's workspace with " + std::to_string(n_orb) +
                                    " orbitals and max_pairs " + std::to_string(span) + " needs " +
                                    std::to_string(bytes_for(1)) + " bytes, beyond the scratch array's " +
                                    std::to_string(kScratchBytes));
-  }
   while (lo < hi) {   // largest k in [1, hi] that fits
     const long long mid = (lo + hi + 1) / 2;
     if (bytes_for(mid) <= kScratchBytes) lo = mid; else hi = mid - 1;
   }
   const long long k = lo;
   const int g = (int)std::min<long long>(k, max_groups);
-  scratch_carve(P, base, n_orb, k, g, &w);
+  scratch_carve(P, base, n_orb, k, g, plain, &w);
   if (!P->on_scratch) {
     P->own_work = get_work(P);
     P->on_scratch = true;
   }
   put_work(P, w);
-  P->no_alloc = true;
-  P->batch_limit = k;
-  P->slot_limit = g;
-  const exx_status st = exx_eval(P, n_orb, orbitals, dt, centres, R_PE_orb, d_subset, n_subset, E_xx, D_xx, sigma);
-  P->no_alloc = false;
-  P->batch_limit = 0;
-  P->slot_limit = 0;
-  P->pcg_off = false;
-  return st;
+  ScratchGuard guard(P, k, g, plain);
+  return exx_eval(P, n_orb, orbitals, dt, centres, R_PE_orb, d_subset, n_subset, E_xx, D_xx, sigma);
 }
 
 exx_status exx_count_pairs(exx_plan_t P, int n_orb, const double* centres, const double* R_PE_orb,

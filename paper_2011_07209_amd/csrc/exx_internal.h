@@ -322,7 +322,7 @@ struct exx_plan_s {
   std::vector<int> class_depth;    // ... and load depth
   std::vector<double> class_delta; // ... and (mixed) reliable-update threshold; 0: the plan's
   std::vector<char> class_pcg;     // 1: the class runs the preconditioned CG (pcg_impl.h)
-  bool pcg_off = false;            // this call's scratch array has no room for its vectors
+  bool plain_call = false;         // this call's scratch array has no room for its vectors: the plain CG for every class
   int n_cus = 1;
   int solve_threads = 1024, solve_depth = 1;   // CG variant in use
   bool tuned = false;
