@@ -65,7 +65,8 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "solve_traffic.json")
 KERNEL_SOURCES = ["paper_2011_07209_amd/csrc/solve_impl.h", "paper_2011_07209_amd/csrc/solve.hip",
                   "paper_2011_07209_amd/csrc/solve_n1.hip", "paper_2011_07209_amd/csrc/solve_n2.hip",
                   "paper_2011_07209_amd/csrc/solve_n3.hip", "paper_2011_07209_amd/csrc/exx_internal.h",
-                  "paper_2011_07209_amd/csrc/plan_geometry.cpp", "paper_2011_07209_amd/csrc/pcg_impl.h"]
+                  "paper_2011_07209_amd/csrc/plan_geometry.cpp", "paper_2011_07209_amd/csrc/pcg_impl.h",
+                  "paper_2011_07209_amd/csrc/pcg_cols.h"]
 MOLECULES = {"tiny16": 4, "water64": 64, "water128": 128, "water256": 256, "water512": 512, "hex64": 64,
              "tri64": 64}   # molecule-equivalents (4 orbitals each)
 D_CHECK_ROWS = 16   # orbitals whose D the mixed/FP64 comparison uses

@@ -40,6 +40,7 @@
 
 #include <type_traits>
 
+#include "pcg_cols.h"
 #include "solve_impl.h"
 
 namespace exx {
@@ -152,30 +153,6 @@ __device__ __forceinline__ int fresh(int v) {
   return v;
 }
 
-// A column of the sphere, as a sweep step uses it.
-template <bool GEN>
-struct PCol {
-  int hi, lo;   // its planes: -hi .. hi (no column: hi < 0), in a general cell lo .. hi
-  int col;      // slot within a plane
-  int low;      // LDS plane position, less the NS rows that the stencil reaches up
-  // whether sweep plane z holds a point of it (in an orthorhombic cell one
-  // comparison with a scalar)
-  __device__ __forceinline__ bool valid(int z) const {
-    if constexpr (GEN)
-      return z >= lo && z <= hi;
-    else
-      return abs(z) <= hi;
-  }
-  __device__ __forceinline__ bool has() const { return GEN ? lo <= hi : hi >= 0; }
-  // whether a plane from z - d to z + d holds one (no column: no plane, or none that counts)
-  __device__ __forceinline__ bool near(int z, int d) const {
-    if constexpr (GEN)
-      return z + d >= lo && z - d <= hi;
-    else
-      return abs(z) <= hi + d;
-  }
-};
-
 // Columns of the sphere owned by a thread, t, t + NT, ... of the class's real
 // columns.  Only what the sweeps cannot recompute in a few instructions is
 // kept: the sweeps' windows need the registers.  PK (FP64, whose windows take
@@ -231,7 +208,8 @@ __device__ __forceinline__ void pcg_cols(const ClassDev& C, int cx, int cy, PCol
 #pragma unroll
   for (int c = 0; c < CPT; ++c) {
     const int k = threadIdx.x + c * NT;
-    cl.put(c, -1, 1, 0, 0);
+    constexpr PCol<GEN> none = PCol<GEN>::none();
+    cl.put(c, none.hi, none.lo, none.col, none.low);
     cl.re[c] = 0;
     if (k < C.n_fin) {
       const int4 f = C.fin_cols[k];
