@@ -618,14 +618,16 @@ double cell_strain(const double h[9], const double h0[9]) {
 
 // Moment and boundary tables of every class for the offset map of g, into the
 // class block (same sizes as at assembly); in place for every stream when it
-// returns.
+// returns.  On the null stream, as the copies that made them before: it waits
+// for evaluations and graph replays that were enqueued there, or on a blocking
+// stream that the plan was bound to earlier, and still read the old tables.
 exx_status rewrite_moment_tables(exx_plan_t P, const Geo& g) {
   const bool mixed = P->opt.precision == EXX_PREC_MIXED;
   int mom_rows = 0, mom_mfma_rows = 0;
   moment_layout(P->l_max, mixed, &mom_rows, &mom_mfma_rows);
   for (size_t k = 0; k < P->classes.size(); ++k)
-    EXX_HIP(P, launch_cell_tables(g, P->class_dev_host[k], mixed, mom_rows, P->stream));
-  EXX_HIP(P, hipStreamSynchronize(P->stream));
+    EXX_HIP(P, launch_cell_tables(g, P->class_dev_host[k], mixed, mom_rows, nullptr));
+  EXX_HIP(P, hipStreamSynchronize(nullptr));
   return EXX_OK;
 }
 
