@@ -67,7 +67,9 @@ typedef struct {
   int stencil_n;              /* half-width n of the axis stencils, 1..3 (Sec. III C,
                                  eq. d2_1; the paper's default is 3)               */
   int precision;              /* exx_precision                                      */
-  double cg_tol;              /* stop when ||r||_2 <= cg_tol ||b||_2 (FP64 residual)  */
+  double cg_tol;              /* stop when ||r||_2 <= cg_tol ||b||_2 (FP64 residual);
+                                 FP64 plans below 1e-14 solve without the
+                                 preconditioner                                    */
   int cg_max_iter;            /* per solve; hitting it is reported as EXX_ENOCONV
                                  (a pair that converges on its last permitted
                                  iteration counts as converged).  A cap below 8

@@ -952,6 +952,20 @@ exx_status assemble_cell(exx_plan_t P, const double h[9]) {
   return EXX_OK;
 }
 
+// Whether the coarse residuals of the preconditioned CG stay accurate to the
+// end of a recursion: they are followed from its first residual, so their
+// rounding stays at eps of that one's norm.  Solves that take the recursion's
+// residual down to that size run the plain CG.  Measured (spheres of 40 points
+// across, four cells): FP64 to 1e-15 converges in as many iterations as the
+// rate to 1e-10 foretells, to 1e-16 it ends in a breakdown with an infinite
+// residual, the plain CG converges.  A mixed recursion ends at its update
+// threshold or at the tolerance: 1e-6 takes 8% more iterations than 1e-2, at
+// 1e-8 each restart breaks down before its first update.
+bool pcg_accurate(const exx_options& opt) {
+  if (opt.precision != EXX_PREC_MIXED) return opt.cg_tol >= 1e-14;
+  return opt.refine_delta <= 0.0 || std::max(opt.refine_delta, opt.cg_tol) >= 1e-6;
+}
+
 // Default CG variant of each class (measured on MI355X): 1024 threads up to
 // three columns each for orthorhombic cells (1024 x 4 spills), up to four for
 // general cells (whose passes keep fewer values per column), else 512; quad
@@ -975,13 +989,14 @@ void default_solve_variants(exx_plan_t P) {
     // The preconditioned CG wherever its buffers fit, unless solve_depth names a
     // load depth of the plain CG (the sweep has one) or cg_max_iter lies below
     // twice what the plain CG needs (about four iterations per point of the
-    // sphere's diameter): such a cap asks for that many plain CG steps.
+    // sphere's diameter): such a cap asks for that many plain CG steps; nor
+    // where rounding would spoil it (pcg_accurate).
     // Untuned, quad classes of mixed plans take the sweep without a stored q (768
     // threads, or 512), other classes 1024 threads up to 3 columns each; FP64
     // in orthorhombic cells up to 2, since three columns' windows spill to scratch
     // memory there (2,957 columns, 2,356 pairs: 178 ms against 152 ms with 512;
     // hexagonal, where the sweep branches: 64 ms against 84 ms, 533 pairs).
-    P->class_pcg[k] = opt.solve_depth == 0 && opt.cg_max_iter >= 8 * (2 * P->classes[k].Zmax + 1) &&
+    P->class_pcg[k] = opt.solve_depth == 0 && pcg_accurate(opt) && opt.cg_max_iter >= 8 * (2 * P->classes[k].Zmax + 1) &&
                       pcg_supported(P->geo, P->classes[k], opt.precision == EXX_PREC_MIXED);
     if (P->class_pcg[k]) {
       const int cols = (int)P->classes[k].fin_cols.size();
