@@ -98,8 +98,10 @@ typedef struct {
                                  tuned/default); 768 applies to quad-layout
                                  classes of at most 768 runs only, other classes
                                  keep their default                              */
-  int solve_depth;            /* 0: preconditioned CG (plain where its buffers do
-                                 not fit, at the tuned/default depth); 1 or 2:
+  int solve_depth;            /* 0: preconditioned CG (plain, at the tuned/default
+                                 depth, where its buffers do not fit, on spheres
+                                 of fewer than five to seven points from centre to
+                                 surface, and see cg_tol and cg_max_iter); 1 or 2:
                                  plain CG with that many planes of loads in
                                  flight ahead of use; cells with arms leaving the
                                  sweep plane have depth 1 only (reported as 1)    */

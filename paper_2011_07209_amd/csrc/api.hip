@@ -966,6 +966,19 @@ bool pcg_accurate(const exx_options& opt) {
   return opt.refine_delta <= 0.0 || std::max(opt.refine_delta, opt.cg_tol) >= 1e-6;
 }
 
+// Whether a class has enough points across for the preconditioner to pay: its
+// coarse phase and wider steps cost as much as several plain iterations, and
+// the plain CG's count grows with the points from the centre to the surface
+// along the sphere's narrowest grid axis, m.  Plain over preconditioned time,
+// 700 to 1,550 pairs: FP64 orthorhombic m = 6 0.80 to 0.93, 7 1.01 to 1.19 (n = 1
+// to 3); general 5 0.86 to 1.11, 6 1.02 to 1.31; mixed (the cells' range) n = 1 6
+// 0.89 to 1.14, 7 1.13 to 1.39; n = 2 5 0.87 to 1.08, 6 0.98 to 1.22; n = 3 4 0.75 to
+// 0.94, 5 1.06 to 1.18.
+bool pcg_pays(const Geo& g, const ClassHost& C, bool mixed) {
+  const int m = std::min(std::min(C.Rc[0], C.Rc[1]), C.Zmax);
+  return m >= (mixed ? 8 - g.n : g.gen ? 6 : 7);
+}
+
 // Default CG variant of each class (measured on MI355X): 1024 threads up to
 // three columns each for orthorhombic cells (1024 x 4 spills), up to four for
 // general cells (whose passes keep fewer values per column), else 512; quad
@@ -990,14 +1003,16 @@ void default_solve_variants(exx_plan_t P) {
     // load depth of the plain CG (the sweep has one) or cg_max_iter lies below
     // twice what the plain CG needs (about four iterations per point of the
     // sphere's diameter): such a cap asks for that many plain CG steps; nor
-    // where rounding would spoil it (pcg_accurate).
+    // where rounding would spoil it (pcg_accurate) or the sphere is too small
+    // (pcg_pays).
     // Untuned, quad classes of mixed plans take the sweep without a stored q (768
     // threads, or 512), other classes 1024 threads up to 3 columns each; FP64
     // in orthorhombic cells up to 2, since three columns' windows spill to scratch
     // memory there (2,957 columns, 2,356 pairs: 178 ms against 152 ms with 512;
     // hexagonal, where the sweep branches: 64 ms against 84 ms, 533 pairs).
+    const bool mixed = opt.precision == EXX_PREC_MIXED;
     P->class_pcg[k] = opt.solve_depth == 0 && pcg_accurate(opt) && opt.cg_max_iter >= 8 * (2 * P->classes[k].Zmax + 1) &&
-                      pcg_supported(P->geo, P->classes[k], opt.precision == EXX_PREC_MIXED);
+                      pcg_pays(P->geo, P->classes[k], mixed) && pcg_supported(P->geo, P->classes[k], mixed);
     if (P->class_pcg[k]) {
       const int cols = (int)P->classes[k].fin_cols.size();
       P->class_threads[k] = t ? t
