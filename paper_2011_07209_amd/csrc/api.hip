@@ -1006,19 +1006,23 @@ void default_solve_variants(exx_plan_t P) {
     // where rounding would spoil it (pcg_accurate) or the sphere is too small
     // (pcg_pays).
     // Untuned, quad classes of mixed plans take the sweep without a stored q (768
-    // threads, or 512), other classes 1024 threads up to 3 columns each; FP64
-    // in orthorhombic cells up to 2, since three columns' windows spill to scratch
-    // memory there (2,957 columns, 2,356 pairs: 178 ms against 152 ms with 512;
-    // hexagonal, where the sweep branches: 64 ms against 84 ms, 533 pairs).
+    // threads, or 512: the workgroups of their fused plain sweeps; tuned, mostly
+    // 1024: 20.3 ms against 24.5 ms, 2,957 columns, 366 pairs), other classes 1024
+    // threads.  FP64 in orthorhombic cells takes 512 with six columns each in place
+    // of three, whose windows spill to scratch memory (2,957 columns, 2,356 pairs:
+    // 178 ms against 152 ms with 512; hexagonal, where the sweep branches: 64 ms
+    // against 84 ms, 533 pairs), but not with eight in place of four (3,249
+    // columns, 366 pairs: 65.3 ms against 67.4 ms with 512; mixed in columns, 4,009:
+    // 33.8 against 48.3; triclinic FP64, spheres of 11% more points: 98 against 124).
     const bool mixed = opt.precision == EXX_PREC_MIXED;
     P->class_pcg[k] = opt.solve_depth == 0 && pcg_accurate(opt) && opt.cg_max_iter >= 8 * (2 * P->classes[k].Zmax + 1) &&
                       pcg_pays(P->geo, P->classes[k], mixed) && pcg_supported(P->geo, P->classes[k], mixed);
     if (P->class_pcg[k]) {
       const int cols = (int)P->classes[k].fin_cols.size();
       P->class_threads[k] = t ? t
-                            : P->classes[k].quads && opt.precision == EXX_PREC_MIXED ? (nc <= 4 * 768 ? 768 : 512)
-                            : cols <= ((opt.precision == EXX_PREC_FP64 && !P->geo.gen) ? 2 : 3) * 1024 ? 1024
-                                                                                                                   : 512;
+                            : P->classes[k].quads && mixed                       ? (nc <= 4 * 768 ? 768 : 512)
+                            : !mixed && !P->geo.gen && pcg_cpt(cols, 1024) == 3 ? 512
+                                                                                : 1024;
       P->class_depth[k] = 1;
       continue;
     }
