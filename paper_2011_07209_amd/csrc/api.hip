@@ -334,6 +334,20 @@ void class_solve_args(exx_plan_t P, int k, SolveArgs* a) {
   }
 }
 
+// The CG variant that class k runs in this call: the plan's, or in a call that
+// runs the plain CG for every class the one that it chose for that.
+CgVariant class_variant(exx_plan_t P, int k, bool plain_call) {
+  if (plain_call) return P->plain_variants[k];
+  return {P->class_threads[k], P->class_depth[k], P->class_groups[k]};
+}
+
+// The class with the most columns, whose variant exx_stats reports as the plan's.
+int widest_class(exx_plan_t P) {
+  return (int)(std::max_element(P->classes.begin(), P->classes.end(),
+                                [](const ClassHost& a, const ClassHost& b) { return a.n_cols < b.n_cols; }) -
+               P->classes.begin());
+}
+
 exx_status apply_solve_variants(exx_plan_t P) {
   const size_t ncls = P->classes.size();
   P->class_groups.assign(ncls, 0);
@@ -351,10 +365,7 @@ exx_status apply_solve_variants(exx_plan_t P) {
     P->slot_ws = nullptr;
   }
   P->n_slots = slots;
-  // the variant reported by exx_stats: that of the class with the most columns
-  const int big = (int)(std::max_element(P->classes.begin(), P->classes.end(),
-                                         [](const ClassHost& a, const ClassHost& b) { return a.n_cols < b.n_cols; }) -
-                        P->classes.begin());
+  const int big = widest_class(P);
   P->solve_threads = P->class_threads[big];
   P->solve_depth = P->class_depth[big];
   return EXX_OK;
@@ -390,11 +401,12 @@ exx_status launch_solves(exx_plan_t P, SolveArgs a, hipStream_t s) {
   for (int k = ncls - 1; k >= 0;) {
     int n_cols = P->classes[k].n_cols, zmax = P->classes[k].Zmax;
     a.cls_id = ncls > 1 ? k : -1;
-    a.threads = P->class_threads[k];
-    a.depth = P->class_depth[k];
+    const CgVariant v = class_variant(P, k, P->plain_call);
+    a.threads = v.threads;
+    a.depth = v.depth;
     if (P->class_delta[k] > 0.0) a.delta = P->class_delta[k];   // chosen by the autotuner
     class_solve_args(P, k, &a);
-    long long groups = P->class_groups[k];
+    long long groups = v.groups;
     int lo = k;
     while (a.pcg_cols > 0 && lo > 0 && P->class_pcg[lo - 1] && P->class_threads[lo - 1] == a.threads) {
       const ClassHost& C = P->classes[lo - 1];
@@ -979,7 +991,15 @@ bool pcg_pays(const Geo& g, const ClassHost& C, bool mixed) {
   return m >= (mixed ? 8 - g.n : g.gen ? 6 : 7);
 }
 
-// Default CG variant of each class (measured on MI355X): 1024 threads up to
+// The workgroup size that solve_threads asks for, where class k can run it, or 0.
+int asked_threads(exx_plan_t P, int k) {
+  const int t = P->opt.solve_threads;
+  const ClassHost& C = P->classes[k];
+  if (t == 512 || t == 1024 || (t == 768 && C.quads && C.n_cols <= 4 * 768)) return t;
+  return 0;
+}
+
+// Default variant of class k's plain CG (measured on MI355X): 1024 threads up to
 // three columns each for orthorhombic cells (1024 x 4 spills), up to four for
 // general cells (whose passes keep fewer values per column), else 512; quad
 // layout classes of mixed plans 768 threads (one run each) where the runs fit,
@@ -987,18 +1007,56 @@ bool pcg_pays(const Geo& g, const ClassHost& C, bool mixed) {
 // threads; an explicit solve_threads that can run the class is kept.  FP64
 // loads one plane ahead, mixed two (512-thread quad classes, and cells with
 // arms leaving the sweep plane, one).
+CgVariant plain_default(exx_plan_t P, int k) {
+  const exx_options& opt = P->opt;
+  const ClassHost& C = P->classes[k];
+  const bool mixed = opt.precision == EXX_PREC_MIXED;
+  CgVariant v{asked_threads(P, k), opt.solve_depth > 0 ? opt.solve_depth : mixed ? 2 : 1, 0};
+  if (C.quads) {
+    // mixed plans fuse each pass B with the next pass A in workgroups of
+    // 768 (one run per thread) or 512 threads (two runs per thread)
+    if (!v.threads) v.threads = mixed ? (C.n_cols <= 4 * 768 ? 768 : 512) : 1024;
+    // two runs per thread: loads one plane ahead (the registers of a
+    // second plane of loads cost more than they hide)
+    if (v.threads == 512 && opt.solve_depth == 0) v.depth = 1;
+  } else {
+    if (!v.threads) v.threads = C.n_cols <= (P->geo.gen ? 4 : 3) * 1024 ? 1024 : 512;
+    if (tilted_arms(P->geo)) v.depth = 1;
+  }
+  return v;
+}
+
+// The variants of a call that runs the plain CG for every class: the default
+// one where the plan runs the preconditioned CG (whose workgroups the plain CG
+// may not have an instance of), else the plan's.
+exx_status set_plain_variants(exx_plan_t P) {
+  const bool mixed = P->opt.precision == EXX_PREC_MIXED;
+  P->plain_variants.clear();
+  for (int k = 0; k < (int)P->classes.size(); ++k) {
+    CgVariant v = class_variant(P, k, false);
+    if (P->class_pcg[k]) {
+      const ClassHost& C = P->classes[k];
+      v = plain_default(P, k);
+      const int per_cu = solve_groups_per_cu(P->geo, C.n_cols, C.Zmax, mixed, C.quads, v.threads, v.depth);
+      if (per_cu < 1) return fail(P, EXX_EDEVICE, "solve kernel cannot be resident (occupancy 0)");
+      v.groups = P->opt.solve_groups > 0 ? P->opt.solve_groups : P->n_cus * per_cu;
+    }
+    P->plain_variants.push_back(v);
+  }
+  return EXX_OK;
+}
+
+// Default solver and CG variant of each class.
 void default_solve_variants(exx_plan_t P) {
   const exx_options& opt = P->opt;
-  const int dp = opt.solve_depth > 0 ? opt.solve_depth : (opt.precision == EXX_PREC_MIXED ? 2 : 1);
-  const int cpt = P->geo.gen ? 4 : 3;
-  P->class_threads.assign(P->classes.size(), 1024);
-  P->class_depth.assign(P->classes.size(), dp);
-  P->class_delta.assign(P->classes.size(), 0.0);
-  P->class_pcg.assign(P->classes.size(), 0);
-  for (size_t k = 0; k < P->classes.size(); ++k) {
-    const int nc = P->classes[k].n_cols;
-    int t = (opt.solve_threads == 512 || opt.solve_threads == 1024) ? opt.solve_threads : 0;
-    if (P->classes[k].quads && opt.solve_threads == 768 && nc <= 4 * 768) t = 768;
+  const bool mixed = opt.precision == EXX_PREC_MIXED;
+  const size_t ncls = P->classes.size();
+  P->class_threads.assign(ncls, 1024);
+  P->class_depth.assign(ncls, 1);
+  P->class_delta.assign(ncls, 0.0);
+  P->class_pcg.assign(ncls, 0);
+  for (size_t k = 0; k < ncls; ++k) {
+    const ClassHost& C = P->classes[k];
     // The preconditioned CG wherever its buffers fit, unless solve_depth names a
     // load depth of the plain CG (the sweep has one) or cg_max_iter lies below
     // twice what the plain CG needs (about four iterations per point of the
@@ -1014,29 +1072,20 @@ void default_solve_variants(exx_plan_t P) {
     // against 84 ms, 533 pairs), but not with eight in place of four (3,249
     // columns, 366 pairs: 65.3 ms against 67.4 ms with 512; mixed in columns, 4,009:
     // 33.8 against 48.3; triclinic FP64, spheres of 11% more points: 98 against 124).
-    const bool mixed = opt.precision == EXX_PREC_MIXED;
-    P->class_pcg[k] = opt.solve_depth == 0 && pcg_accurate(opt) && opt.cg_max_iter >= 8 * (2 * P->classes[k].Zmax + 1) &&
-                      pcg_pays(P->geo, P->classes[k], mixed) && pcg_supported(P->geo, P->classes[k], mixed);
+    P->class_pcg[k] = opt.solve_depth == 0 && pcg_accurate(opt) && opt.cg_max_iter >= 8 * (2 * C.Zmax + 1) &&
+                      pcg_pays(P->geo, C, mixed) && pcg_supported(P->geo, C, mixed);
     if (P->class_pcg[k]) {
-      const int cols = (int)P->classes[k].fin_cols.size();
-      P->class_threads[k] = t ? t
-                            : P->classes[k].quads && mixed                       ? (nc <= 4 * 768 ? 768 : 512)
-                            : !mixed && !P->geo.gen && pcg_cpt(cols, 1024) == 3 ? 512
-                                                                                : 1024;
-      P->class_depth[k] = 1;
-      continue;
-    }
-    if (P->classes[k].quads) {
-      // mixed plans fuse each pass B with the next pass A in workgroups of
-      // 768 (one run per thread) or 512 threads (two runs per thread)
-      if (!t) t = opt.precision == EXX_PREC_MIXED ? (nc <= 4 * 768 ? 768 : 512) : 1024;
+      int t = asked_threads(P, (int)k);
+      if (!t && C.quads && mixed)
+        t = C.n_cols <= 4 * 768 ? 768 : 512;
+      else if (!t)
+        t = !mixed && !P->geo.gen && pcg_cpt((int)C.fin_cols.size(), 1024) == 3 ? 512 : 1024;
       P->class_threads[k] = t;
-      // two runs per thread: loads one plane ahead (the registers of a
-      // second plane of loads cost more than they hide)
-      if (t == 512 && opt.solve_depth == 0) P->class_depth[k] = 1;
       continue;
     }
-    P->class_threads[k] = t ? t : (nc <= cpt * 1024 ? 1024 : 512);
+    const CgVariant v = plain_default(P, (int)k);
+    P->class_threads[k] = v.threads;
+    P->class_depth[k] = v.depth;
   }
 }
 
@@ -1369,6 +1418,7 @@ exx_status exx_eval(exx_plan_t P, int n_orb, const void* orbitals, exx_dtype dt,
   if (!P->no_alloc) use_own_work(P);
   P->timing_valid = false;
   P->last_captured = capturing;
+  P->last_plain = P->plain_call;
   P->solve_ev_used = 0;
   P->mom_ev_used = 0;
   CaptureGuard guard(P, capturing);   // dev_alloc refuses while the stream is captured
@@ -1613,6 +1663,12 @@ exx_status exx_eval_noalloc(exx_plan_t P, int n_orb, const void* orbitals, exx_d
     return scratch_carve(P, nullptr, n_orb, k, (int)std::min<long long>(k, max_groups), plain, &w);
   };
   plain = bytes_for(1) > kScratchBytes;
+  if (plain) {
+    exx_status ps = set_plain_variants(P);
+    if (ps != EXX_OK) return ps;
+    max_groups = 1;
+    for (const CgVariant& v : P->plain_variants) max_groups = std::max(max_groups, v.groups);
+  }
   if (bytes_for(1) > kScratchBytes)
     return fail(P, EXX_EINVAL, "exx_eval_noalloc: one pair's workspace with " + std::to_string(n_orb) +
                                    " orbitals and max_pairs " + std::to_string(span) + " needs " +
@@ -1754,8 +1810,8 @@ exx_status exx_stats_fetch(exx_plan_t P, exx_stats* out) {
     for (const ClassHost& C : P->classes) nq += C.quads ? 1 : 0;
     out->cg_layout = nq == 0 ? 1 : (nq == (int)P->classes.size() ? 2 : 3);
   }
-  out->solve_threads = P->solve_threads;
-  out->solve_depth = P->solve_depth;
+  out->solve_threads = class_variant(P, widest_class(P), P->last_plain).threads;
+  out->solve_depth = class_variant(P, widest_class(P), P->last_plain).depth;
   out->tune_ms = P->tune_ms;
   out->pairs_kept = (long long)st[4];
   out->graph_recorded = P->last_captured ? 1 : 0;
@@ -1767,8 +1823,8 @@ exx_status exx_stats_fetch(exx_plan_t P, exx_stats* out) {
   out->t_pairlist_ms = P->last_pairlist_ms;
   out->t_reduce_ms = P->last_reduce_ms;
   for (int k = 0; k < (int)P->classes.size() && k < kMaxClasses; ++k) {
-    out->class_threads[k] = P->class_threads[k];
-    out->class_depth[k] = P->class_depth[k];
+    out->class_threads[k] = class_variant(P, k, P->last_plain).threads;
+    out->class_depth[k] = class_variant(P, k, P->last_plain).depth;
     out->class_layout[k] = P->classes[k].quads ? 2 : 1;
     out->class_pairs[k] = P->last_class_pairs[k];
     out->class_refine_delta[k] = P->opt.precision != EXX_PREC_MIXED ? 0.0

@@ -152,6 +152,11 @@ struct PairDev {
   int cls;
 };
 
+// A CG variant: workgroup size, planes of loads in flight, persistent workgroups.
+struct CgVariant {
+  int threads, depth, groups;
+};
+
 struct ClassHost {
   double R_PE = 0;
   int n_cols = 0, Zmax = 0;
@@ -322,7 +327,10 @@ struct exx_plan_s {
   std::vector<int> class_depth;    // ... and load depth
   std::vector<double> class_delta; // ... and (mixed) reliable-update threshold; 0: the plan's
   std::vector<char> class_pcg;     // 1: the class runs the preconditioned CG (pcg_impl.h)
-  bool plain_call = false;         // this call's scratch array has no room for its vectors: the plain CG for every class
+  bool plain_call = false;         // this call's scratch array has no room for its vectors: the plain CG for every
+                                   // class, with plain_variants
+  bool last_plain = false;         // the last evaluation was such a call
+  std::vector<exx::CgVariant> plain_variants;
   int n_cus = 1;
   int solve_threads = 1024, solve_depth = 1;   // CG variant in use
   bool tuned = false;
