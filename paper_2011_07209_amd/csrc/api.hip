@@ -114,6 +114,7 @@ exx_status dev_alloc(exx_plan_t P, T** p, size_t count, const char* what) {
   if (count == 0) return EXX_OK;
   hipError_t e = hipMalloc((void**)p, count * sizeof(T));
   if (e != hipSuccess) {
+    (void)hipGetLastError();   // the next launch's check would report it
     *p = nullptr;
     return fail(P, EXX_ENOMEM, std::string("device allocation failed: ") + what);
   }
@@ -378,13 +379,22 @@ exx_status select_solve(exx_plan_t P, int threads, int depth, int cls) {
   return apply_solve_variants(P);
 }
 
+// The CG vectors of the persistent workgroups; of fewer workgroups where the
+// device has no room for all (the preconditioned CG's are two to three times the
+// plain CG's).
 exx_status ensure_slots(exx_plan_t P) {
   if (P->slot_ws) return EXX_OK;
-  char* sw = nullptr;
   const long long sb = plan_slot_bytes(P, false);
-  if (dev_alloc(P, &sw, (size_t)P->n_slots * sb, "CG vectors")) return EXX_ENOMEM;
-  P->slot_ws = sw;
-  return EXX_OK;
+  for (;;) {
+    char* sw = nullptr;
+    const exx_status st = dev_alloc(P, &sw, (size_t)P->n_slots * sb, "CG vectors");
+    if (st == EXX_OK) {
+      P->slot_ws = sw;
+      return EXX_OK;
+    }
+    if (st != EXX_ENOMEM || P->n_slots <= 1) return EXX_ENOMEM;
+    P->n_slots = (P->n_slots + 1) / 2;
+  }
 }
 
 // The CG solve of a batch: one persistent launch per sphere class, in
@@ -424,7 +434,7 @@ exx_status launch_solves(exx_plan_t P, SolveArgs a, hipStream_t s) {
     }
     a.cls_lo = ncls > 1 ? lo : -1;
     EXX_HIP(P, launch_set_int(P->queue, 0, s));
-    groups = std::min(groups, a.npair);
+    groups = std::min<long long>(std::min(groups, a.npair), P->n_slots);
     if (P->slot_limit > 0) groups = std::min<long long>(groups, P->slot_limit);   // CG slots of the scratch layout
     EXX_HIP(P, launch_solve(a, n_cols, zmax, (int)groups, s));
     k = lo - 1;
@@ -470,7 +480,7 @@ exx_status autotune_solve(exx_plan_t P, const SolveArgs& base, long long nb, hip
       if (st != EXX_OK) return st;
       st = ensure_slots(P);
       if (st != EXX_OK) return st;
-      const long long sample = std::min<long long>(hi - lo, P->class_groups[k]);
+      const long long sample = std::min<long long>(hi - lo, std::min(P->class_groups[k], P->n_slots));
       SolveArgs a = base;
       a.npair = lo + sample - base.p0;   // batch rows up to the end of the sample
       a.slot_ws = P->slot_ws;
