@@ -1,5 +1,5 @@
-// A column of the sphere as a sweep step of the preconditioned CG uses it
-// (pcg_impl.h), in code that the host can also run.
+// Parts of the preconditioned CG (pcg_impl.h) in code that the host can also run:
+// a column of the sphere as a sweep step uses it, and the update of the solution.
 #pragma once
 
 #include "exx_internal.h"
@@ -34,5 +34,16 @@ struct PCol {
     return z + d >= lo && z - d <= hi;
   }
 };
+
+// y + the steps w_i v_i, in the precision X of the solution they are added to: a
+// reliable update of the mixed solve folds its FP32 vectors into the FP64
+// solution without rounding their sum to FP32 first.
+template <typename X, typename T>
+__host__ __device__ constexpr X pcg_add_steps(T y, const X (&w)[kPcgRing], const T (&v)[kPcgRing]) {
+  X s = (X)y;
+#pragma unroll
+  for (int i = 0; i < kPcgRing; ++i) s += w[i] * (X)v[i];
+  return s;
+}
 
 }  // namespace exx
