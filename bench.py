@@ -324,6 +324,7 @@ def run_precision(exx, torch, synth, cfg, orbs, bufs, precision, steps, warmup, 
         solve_ms = s_last["solve_ms_total"] - s0["solve_ms_total"]
         alg = s_last["cg_alg_bytes_total"] - s0["cg_alg_bytes_total"]
         achieved = (alg / max(launches, 1)) / (solve_ms / max(launches, 1) / 1000.0) / 1e9 if solve_ms > 0 else 0.0
+        # (every class of the workloads runs the preconditioned CG: their tolerance, iteration cap and spheres allow it)
         cg = {"bound": "hbm", "kernel": "k_pcg_mixed" if precision == "mixed" else "k_pcg",
               "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
               "traffic": stored_traffic(cfg.key, precision, s_last["solve_threads"], s_last["solve_depth"],

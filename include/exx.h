@@ -97,7 +97,8 @@ typedef struct {
   int solve_threads;          /* CG workgroup size, 512, 768 or 1024 (0:
                                  tuned/default); 768 applies to quad-layout
                                  classes of at most 768 runs only, other classes
-                                 keep their default                              */
+                                 keep their default (the autotuner tries it for
+                                 every class of the preconditioned CG)           */
   int solve_depth;            /* 0: preconditioned CG (plain, at the tuned/default
                                  depth, where its buffers do not fit, on spheres
                                  of fewer than five to seven points from centre to
@@ -330,7 +331,8 @@ typedef struct {
    centres of the next exx_eval use h (centres are Cartesian, for the new
    cell).  With reassemble_strain > 0 and a strain above it, the tables are
    rebuilt for h from the plan's radii (new point counts; the warm-start
-   history is dropped).  Waits for the plan's stream; not capturable: HIP
+   history is dropped).  Waits for the plan's stream and, as a copy on the
+   null stream does, for work there and on blocking streams; not capturable: HIP
    graphs recorded before the call keep the old cell and tables, record them
    again.  EXX_EINVAL for a singular or left-handed h, for a non-orthogonal h
    on a plan built without cell_fluctuation for an orthorhombic cell, or when

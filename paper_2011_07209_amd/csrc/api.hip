@@ -909,7 +909,6 @@ exx_status assemble_cell(exx_plan_t P, const double h[9]) {
     D.mg.p2 = (const short4*)put(C.mg_pts[1].data(), C.mg_pts[1].size() * sizeof(short4));
     D.mg.p3 = (const short4*)put(C.mg_pts[2].data(), C.mg_pts[2].size() * sizeof(short4));
     D.mg.p4 = (const short4*)put(C.mg_pts[3].data(), C.mg_pts[3].size() * sizeof(short4));
-    if (!D.mg.c1cols || !D.mg.c1start || !D.mg.p1) D.mg.n_c1 = 0;
     D.mom_rows = mom_rows;
     std::vector<double> btab;
     build_boundary_table(C, g.A, g.ylm_norm, P->l_max, &btab);
@@ -1320,7 +1319,6 @@ exx_status exx_plan(const double h[9], const int grid[3], double R_pair, double 
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, P->device);
   P->n_cus = std::max(1, cus);
   {
-    // defaults measured on MI355X: FP64 1024 x 1, mixed 1024 x 2
     default_solve_variants(P);
     exx_status st = apply_solve_variants(P);
     if (st != EXX_OK) {

@@ -335,7 +335,8 @@ struct exx_plan_s {
   int solve_threads = 1024, solve_depth = 1;   // CG variant in use
   bool tuned = false;
   double tune_ms = 0;
-  void* slot_ws = nullptr;     // [slots] CG vectors: FP64 r, p; mixed: FP64 x, FP32 r, p, y
+  void* slot_ws = nullptr;     // [slots] CG vectors: FP64 r, p; mixed: FP64 x, FP32 r, p, y; preconditioned: see
+                               // PSlot (q is held also where a mixed variant forms it anew)
   int* queue = nullptr;
   double* stats_dev = nullptr;     // the eight values of k_reduce (see launch_reduce)
   int last_n_orb = 0;

@@ -135,10 +135,10 @@ bool finalize_sweep_supported(const Geo& g, long long max_cols);
 hipError_t launch_finalize_sweep(const Geo& g, const Batch& B, long long max_cols, const double* rho_ws,
                                  const double* v_ws, long long rstride, const double* halo_ws, long long hstride,
                                  double* outE, double* outS, hipStream_t s);
-// D^i += v phi_j (and D^j += v phi_i) into row d_slot[i] of D, or row i when
-// d_slot is null; rows with d_slot = -1 are not written.
 // The moment (rows of it) and boundary tables of a class, rewritten for the cell of g.
 hipError_t launch_cell_tables(const Geo& g, const ClassDev& C, bool mixed, int rows, hipStream_t s);
+// D^i += v phi_j (and D^j += v phi_i) into row d_slot[i] of D, or row i when
+// d_slot is null; rows with d_slot = -1 are not written.
 hipError_t launch_dscatter(const Geo& g, const Batch& B, long long max_me, const void* orb, void* D,
                            const int* d_slot, int dt, const double* v_ws, long long rstride, const double* Q_ws,
                            hipStream_t s);

@@ -72,7 +72,6 @@ __device__ __forceinline__ MgU mg_uniform(const MgDev& M) {
 // of accesses in flight is unknown and the compiler waits for all of them,
 // stores of the plane before included (mixed, 2,957 columns, one pair per CU:
 // a solve 9.3 ms against 7.7 ms with 1024 threads).
-// [buffer access]
 struct PBuf {
   __amdgpu_buffer_rsrc_t r;
 };
@@ -94,14 +93,12 @@ __device__ __forceinline__ void bstore(const PBuf& b, unsigned voff, unsigned so
   else
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, v), b.r, voff, soff, 0);
 }
-// [end of buffer access]
 constexpr unsigned kOob = 0x80000000u;
 
 // The general stencil, read anew from the kernel's arguments (one struct, at
 // the start of their segment): the 60 scalar registers that its FP64 constants
 // take are not there for a whole sweep, and kept ones were moved to lanes of
 // vector registers and back (321 moves per two steps of the FP64 sweep).
-// [kernel arguments]
 template <typename T>
 __device__ __forceinline__ GenStencilT<T> gen_args(const SolveKArgs&) {
   typedef const __attribute__((address_space(4))) SolveKArgs KArgs;
@@ -134,7 +131,6 @@ __device__ __forceinline__ GenStencilT<T> gen_args(const SolveKArgs&) {
     copy(k->G);
   return g;
 }
-// [end of kernel arguments]
 
 // A sweep's vectors, as byte offsets into the slot's buffer.  none: kOob before
 // the first direction, when p and q are to read zero, else 0.
@@ -995,7 +991,8 @@ __device__ __forceinline__ T restrict27(const T* B, const int* E, const int* D, 
 // The coarse phase: the residuals of levels 1 and 2, c1 and b2, take the step
 // - alpha P^T q (g1, g2; not with fresh residuals), levels 2 to 4 follow as boxes
 // in LDS, then the correction e1 over the level-1 points.  sums: this
-// thread's parts of r_1.e_1, e_1.g_1 of the e_1 before, and e_1.g_1.  The boxes lie in
+// thread's parts of r_1.e_1, e_1.g_1 of the e_1 before, and e_1.g_1 (and zero:
+// block_sum4 takes four).  The boxes lie in
 // the sweeps' LDS and are cleared at the end (positions off the sphere must read
 // zero there).
 template <int NT, typename T>
